@@ -351,30 +351,90 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_rows_kernel(const uint16_t*
   }
 }
 
-// ----------------------------------------------------------------------------- fp32 (vector)
-// Unfused fp32 path (row kernels finish the layer).  One wave per output column; lanes
-// stride K, rows in groups of 16, wave-reduced.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X, int ldx,
-                                                       const float* __restrict__ W, int M, int N, int K,
-                                                       float* __restrict__ part) {
-  const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-  const int n = blockIdx.x * 4 + wave;
-  if (n >= N) return;
-  const float* w = W + (int64_t)n * K;
-  for (int m0 = 0; m0 < M; m0 += 16) {
-    float acc[16];
+// ----------------------------------------------------------------------------- fp32 MFMA
+// Unfused fp32 path (row kernels finish the layer), on v_mfma_f32_16x16x4f32 (fp32 products and
+// sums).  A small fp32 model's product is bound by latency, not by bytes (0.25-2 MB of weights
+// that stay in L2), so a workgroup takes one 16-column tile and MR 16-row blocks, its eight
+// waves split K, and every load of a wave's K range (up to U steps of 16) is in flight before
+// its first product.  Lane (lq, g) holds four consecutive k of W row lq and of X row lq, one
+// accumulator per element and per odd or even step, so the MFMA chains are K / 256 long (the
+// sums stay as short as a lane-strided sum's); accumulators, then waves, are added pairwise.  One wave per column with the rows read one by one had taken 24-72 us a
+// launch at 17 rows (K 256 and 1024): 377 -> 104 us for the two-layer model's 17-row forward.
+// W and X rows need 4-byte alignment only; K is a multiple of 16; rows past M or N repeat the last.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int MR, int U>
+__global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ X, int ldx,
+                                                                const float* __restrict__ W, int M, int N, int K,
+                                                                float* __restrict__ part) {
+  __shared__ f32x4 red[TILE_WAVES][MR][WAVE];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int lane = threadIdx.x % WAVE, lq = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * MR * 16;
+  const int steps = K / 16;
+  const int s0 = (int)((int64_t)steps * wave / TILE_WAVES), s1 = (int)((int64_t)steps * (wave + 1) / TILE_WAVES);
+  const float* wp = W + (int64_t)min(n0 + lq, N - 1) * K;
+  const float* xp[MR];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    for (int k = lane; k < K; k += WAVE) {
-      const float wv = w[k];
+  for (int m = 0; m < MR; ++m) xp[m] = X + (int64_t)min(m0 + m * 16 + lq, M - 1) * ldx;
+  auto load4 = [&](const float* p, int k) -> f32x4 {
+    if (k < K) return *reinterpret_cast<const f32x4_a4*>(p + k);
+    return f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  f32x4 acc[MR][8];
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (m0 + i < M) acc[i] = fmaf(X[(int64_t)(m0 + i) * ldx + k], wv, acc[i]);
+  for (int m = 0; m < MR; ++m)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[m][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = s0; c < s1; c += U) {
+    f32x4 w[U], x[U][MR];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = c + u < s1 ? (c + u) * 16 + 4 * g : K;   // steps past the wave's range load nothing
+      w[u] = load4(wp, k);
+#pragma unroll
+      for (int m = 0; m < MR; ++m) x[u][m] = load4(xp[m], k);
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float v = wave_sum(acc[i]);
-      if (lane == 0 && m0 + i < M) part[(int64_t)(m0 + i) * N + n] = v;
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int m = 0; m < MR; ++m)
+          acc[m][u % 2 * 4 + e] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e], x[u][m][e], acc[m][u % 2 * 4 + e], 0, 0, 0);
+  }
+#pragma unroll
+  for (int m = 0; m < MR; ++m) {
+    f32x4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      y[r] = ((acc[m][0][r] + acc[m][4][r]) + (acc[m][1][r] + acc[m][5][r])) +
+             ((acc[m][2][r] + acc[m][6][r]) + (acc[m][3][r] + acc[m][7][r]));
+    red[wave][m][lane] = y;
+  }
+  __syncthreads();
+  if (wave < MR) {
+    f32x4 v[TILE_WAVES];
+#pragma unroll
+    for (int w = 0; w < TILE_WAVES; ++w) v[w] = red[w][wave][lane];
+#pragma unroll
+    for (int h = 1; h < TILE_WAVES; h *= 2)
+#pragma unroll
+      for (int w = 0; w < TILE_WAVES; w += 2 * h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[w][r] += v[w + h][r];
+    const f32x4 y = v[0];
+    const int row = m0 + wave * 16 + lq, n = n0 + 4 * g;
+    if (row < M) {
+      float* dst = part + (int64_t)row * N + n;
+      if (n + 4 <= N) {
+        *reinterpret_cast<f32x4_a4*>(dst) = y;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (n + r < N) dst[r] = y[r];
+      }
     }
   }
 }
@@ -469,8 +529,18 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
                        const GemmEpi& epi, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int* splits) {
   ADT_CHECK_ARG(M >= 1 && M <= 128, ADT_E_CAPACITY, "gemm: M=%d outside [1,128]", M);
   if (dtype == ADT_F32) {
-    hipExtLaunchKernelGGL(gemm_f32_kernel, dim3((N + 3) / 4), dim3(256), 0, st, ev0, ev1, 0, (const float*)X, ldx,
-                          (const float*)Wp, M, N, K, part);
+    ADT_CHECK_ARG(K % 16 == 0, ADT_E_SHAPE, "gemm f32: K=%d", K);
+    // one row block per workgroup while that leaves the launch within two rounds of the CUs
+    // (17 rows: 32-256 workgroups), else up to four, so that a tile's weights are read fewer times
+    const int tiles = (N + 15) / 16, mb = (M + 15) / 16;
+    const float *x = (const float*)X, *w = (const float*)Wp;
+#define ADT_GF(MRV, UV)                                                                                               \
+  hipExtLaunchKernelGGL((gemm_f32_kernel<MRV, UV>), dim3(tiles, (mb + MRV - 1) / MRV), dim3(TILE_THREADS), 0, st, ev0, \
+                        ev1, 0, x, ldx, w, M, N, K, part)
+    if ((int64_t)tiles * mb <= 512) ADT_GF(1, 8);
+    else if ((int64_t)tiles * mb <= 1024) ADT_GF(2, 4);
+    else ADT_GF(4, 4);
+#undef ADT_GF
     ADT_LAUNCH_CHECK();
     if (splits) *splits = 1;
     return ADT_OK;

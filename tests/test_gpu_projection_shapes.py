@@ -1,0 +1,58 @@
+"""Verify forwards at the row counts and widths where the projection kernels change their
+tiling (row blocks, column groups, K remainders), against the fp64 oracle on the same model:
+logits within (1e-5, 1e-5) in fp32 and (2e-2, 1e-2) in bf16."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle.decode import Decoder
+from oracle.model import OracleModel
+from oracle.tree import ancestors_and_self, depths
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": (1e-5, 1e-5), "bf16": (2e-2, 1e-2)}
+
+
+@pytest.fixture(scope="module")
+def rt():
+    from paper_2512_21857_amd import runtime
+    assert torch.cuda.is_available()
+    return runtime
+
+
+def _check_verify(rt, cfg, n, seed=0):
+    w = synth.model_weights(cfg)
+    om, dm, pre = OracleModel(cfg, w), rt.DeviceModel(cfg, w), synth.prefix_ids(cfg)
+    sess, dec = rt.DeviceSession(dm, cfg), Decoder(cfg, om, pre)
+    root = sess.prefill(pre)
+    dec.prefill()
+    rng = np.random.default_rng([seed, n])
+    parent = synth.random_parents(rng, n)
+    dep = depths(parent)
+    order = np.argsort(dep, kind="stable")
+    inv = np.argsort(order)
+    parent = np.array([-1 if parent[o] < 0 else inv[parent[o]] for o in order], dtype=np.int32)
+    token = rng.integers(cfg.img_lo, cfg.img_hi, size=n).astype(np.int32)
+    token[0] = root
+    sess.set_tree(parent, token)
+    sess.verify()
+    got = sess.tensors()["logits"].cpu().numpy()
+    L, d = dec.L, depths(parent)
+    keys = [list(range(L)) + [L + j for j in a] for a in ancestors_and_self(parent)]
+    ref, _ = om.target_rows(token, L + d, [L + i for i in range(n)], keys, dec.tcache)
+    lo, hi = cfg.img_lo, cfg.img_hi
+    atol, rtol = TOL[cfg.model.dtype]
+    err = np.abs(got[:, lo:hi] - ref[:, lo:hi])
+    assert np.isfinite(got[:, lo:hi]).all() and (err <= atol + rtol * np.abs(ref[:, lo:hi])).all(), err.max()
+
+
+@pytest.mark.parametrize("ffn,vocab,n", [(1008, 1059, 1), (80, 1057, 16), (1008, 1058, 17), (2048, 1056, 127)])
+def test_verify_f32_odd_shapes(rt, ffn, vocab, n):
+    """K steps that do not divide among the waves, columns past a 16-wide tile, one to four row blocks
+    per workgroup."""
+    cfg = synth.shrink(synth.get_config("tiny"), ffn=ffn, vocab=vocab)
+    _check_verify(rt, cfg, n)
