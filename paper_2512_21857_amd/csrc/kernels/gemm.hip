@@ -351,6 +351,190 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_rows_kernel(const uint16_t*
   }
 }
 
+// ----------------------------------------------------------------------------- 65-128 rows
+// The batch-1 product at 65-128 rows (a guided tree's two branches, a long prompt chunk).  Here
+// gemm_rows_kernel's accumulators allow two column tiles per workgroup, so its workgroups read
+// the M input rows hundreds of times over (up to 1 MB each); what bounds it is that re-read.
+// This kernel takes up to eight tiles per workgroup, one workgroup per CU: the stage of KP
+// k-tiles (T weight tiles and MT input blocks of 1 KB each, both stored in fragment order)
+// comes into a ring of NST LDS slots by global->LDS DMA (no registers stage it), wave
+// (kp, mp) multiplies k-tile kp of every stage by the RB row blocks mp * RB.., and the KP parts
+// meet in LDS at the end, in part order.  The fragments of the next stage are read from LDS
+// while the current ones are multiplied; one barrier per stage says that the stage has landed
+// for every wave (each waits for its own pieces; the newer stages stay in flight) and that the
+// slot refilled next has been read.  RB = 2 at 8 row blocks (five slots of two k-tiles beat
+// two of four, 47 against 57 us for gate/up) and 3 at 6 (one pass of LDS reads less: 41
+// against 48).  LDS reads (64 B a clock and CU) are then about as long as the weight stream.
+// 7B shapes, before -> now: at 122 rows gate/up 78 -> 48 us, LM head (65536) 190 -> 112,
+// down 33 -> 25; at 90 rows 67 -> 41, 166 -> 110, 29 -> 23; LlamaGen-XL down at 120 rows
+// 17.3 -> 8.1 us (six K ranges), LM head 23 -> 15.
+// The DMA and its waits are inline assembly because the compiler would wait for every DMA in
+// flight before each LDS read.
+template <int NI, int D>
+__device__ __forceinline__ void dma_wait_stages(int rem) {   // min(rem, D) stages of NI pieces stay in flight
+  static_assert(NI * D <= 63, "vmcnt");
+  if constexpr (D > 0) {
+    if (rem >= D) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NI * D) : "memory");
+    else dma_wait_stages<NI, D - 1>(rem);
+  } else {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+}
+
+template <int MT, int T, int RB, int NST, bool NORM>
+__global__ __launch_bounds__(TILE_THREADS, 2) void gemm_rows_dma_kernel(const uint16_t* __restrict__ X,
+                                                                        const uint16_t* __restrict__ Wp, int M, int N,
+                                                                        int K, int S, GemmEpi epi) {
+  constexpr int MP = MT / RB, KP = TILE_WAVES / MP;   // row groups, K parts (one wave each)
+  static_assert(MT % RB == 0 && MP * KP == TILE_WAVES, "one wave per row group and K part");
+  constexpr int PK = T + MT;                          // 1 KB pieces per k-tile
+  constexpr int P = PK * KP, NI = (P + TILE_WAVES - 1) / TILE_WAVES;   // pieces per stage, per wave
+  constexpr int SLOT = P * 1024;
+  constexpr int NB = RB * T;                          // 16x16 output blocks per wave
+  constexpr int RED = TILE_WAVES * NB * 1024, RED_SS = NORM ? KP * MT * 64 : 0;   // final sums, over the ring
+  constexpr int LDS = NST * SLOT > RED + RED_SS ? NST * SLOT : RED + RED_SS;
+  static_assert(LDS <= 160 * 1024, "LDS of a CU");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
+  const int KT = K / 32;
+  const int cb = blockIdx.x / S, sp = blockIdx.x % S;
+  const int G = gridDim.x / S, tiles = N / 16;
+  const int t0 = (int)((int64_t)cb * tiles / G), tc = (int)((int64_t)(cb + 1) * tiles / G) - t0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int lane = threadIdx.x % WAVE, lq = lane & 15, g = lane >> 4;
+  const int kp = wave / MP, mp = wave % MP;
+  const int ks0 = (int)((int64_t)KT * sp / S), ks1 = (int)((int64_t)KT * (sp + 1) / S);
+  const int nk = ks1 - ks0, NS = (nk + KP - 1) / KP;
+  const int mt = (M + 15) / 16;
+  const int rot = (int)((blockIdx.x * 37u) % (unsigned)NS);
+  // this wave's pieces of a stage: wave + TILE_WAVES i (past P: the last piece again, into its own place)
+  const char* wbase = (const char*)Wp + ((int64_t)t0 * KT + ks0) * 1024;
+  const char* xbase = (const char*)X + (int64_t)ks0 * mt * 1024;
+  uint32_t off0[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int q = min(wave + TILE_WAVES * i, P - 1) % PK;
+    off0[i] = q < T ? (uint32_t)min(q, tc - 1) * KT : (uint32_t)min(q - T, mt - 1);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+  const uint32_t voff = lane * 16;
+  auto smap = [&](int st) {   // stages in an order that starts elsewhere in every workgroup
+    const int s = st + rot;
+    return s >= NS ? s - NS : s;
+  };
+  int slot_i = 0;
+  auto issue = [&](int st) {
+    const int s = smap(st);
+    const uint32_t d = lds0 + slot_i * SLOT;
+    slot_i = slot_i + 1 == NST ? 0 : slot_i + 1;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int p = min(wave + TILE_WAVES * i, P - 1), q = p % PK;
+      const uint32_t kt = min(s * KP + p / PK, nk - 1);
+      const uint32_t o = voff + (off0[i] + (q < T ? kt : kt * mt)) * 1024;
+      const uint32_t dst = d + p * 1024;
+      // the weights are read once (nt); M0 by s_mov only, which leaves SCC alone
+      if (q < T)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(o), "s"(wbase), "s"(dst)
+                     : "memory", "m0");
+      else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o), "s"(xbase), "s"(dst)
+                     : "memory", "m0");
+    }
+  };
+  f32x4 acc[T][RB];
+  float ss[RB];
+#pragma unroll
+  for (int m = 0; m < RB; ++m) ss[m] = 0.f;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int m = 0; m < RB; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < NST; ++s)
+    if (s < NS) issue(s);
+  struct Fr { bf16x8 w[T], x[RB]; };
+  const unsigned char* rbase = lds + kp * PK * 1024 + lane * 16;
+  int rd = 0;
+  auto frags = [&](Fr& f) {
+    const unsigned char* base = rbase + rd * SLOT;
+    rd = rd + 1 == NST ? 0 : rd + 1;
+#pragma unroll
+    for (int m = 0; m < RB; ++m) f.x[m] = *reinterpret_cast<const bf16x8*>(base + (T + mp * RB + m) * 1024);
+#pragma unroll
+    for (int t = 0; t < T; ++t) f.w[t] = *reinterpret_cast<const bf16x8*>(base + t * 1024);
+  };
+  auto mma = [&](const Fr& f, int st) {
+    if (smap(st) * KP + kp < nk) {
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int m = 0; m < RB; ++m) acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[t], f.x[m], acc[t][m], 0, 0, 0);
+      if (NORM) {
+#pragma unroll
+        for (int m = 0; m < RB; ++m) ss[m] = sumsq8(f.x[m], ss[m]);
+      }
+    }
+  };
+  // stage st + 1 has landed for every wave and stage st has been read by every wave
+  auto step = [&](const Fr& cur, Fr& nxt, int st) {
+    if (st + 1 < NS) {
+      dma_wait_stages<NI, NST - 2>(NS - 2 - st);
+      if (st + NST < NS) issue(st + NST);
+      frags(nxt);
+    }
+    mma(cur, st);
+  };
+  Fr fa, fb;
+  dma_wait_stages<NI, NST - 1>(NS - 1);
+  frags(fa);
+  for (int st = 0; st < NS; st += 2) {
+    step(fa, fb, st);
+    if (st + 1 < NS) step(fb, fa, st + 1);
+  }
+  f32x4* red = reinterpret_cast<f32x4*>(lds);
+  float(*red_ss)[MT][16] = reinterpret_cast<float(*)[MT][16]>(lds + RED);
+  __syncthreads();   // every wave has read its last stage (and no DMA is in flight): the ring is free
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int m = 0; m < RB; ++m) red[(wave * NB + t * RB + m) * WAVE + lane] = acc[t][m];
+  if (NORM) {
+#pragma unroll
+    for (int m = 0; m < RB; ++m) {
+      float v = ss[m];
+      v += __shfl_xor(v, 16, WAVE);
+      v += __shfl_xor(v, 32, WAVE);
+      if (g == 0) red_ss[kp][mp * RB + m][lq] = v;
+    }
+  }
+  __syncthreads();
+  // wave (kp, mp) finishes blocks kp, kp + KP, .. of its row group
+#pragma unroll
+  for (int r = 0; r < (NB + KP - 1) / KP; ++r) {
+    const int b = kp + KP * r;
+    if (b >= NB || b / RB >= tc) continue;
+    f32x4 y = red[(mp * NB + b) * WAVE + lane];
+#pragma unroll
+    for (int w = 1; w < KP; ++w) {
+      const f32x4 v = red[((w * MP + mp) * NB + b) * WAVE + lane];
+      y = f32x4{y[0] + v[0], y[1] + v[1], y[2] + v[2], y[3] + v[3]};
+    }
+    const int mb = mp * RB + b % RB, row = mb * 16 + lq, nt = t0 + b / RB;
+    if (NORM) {
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < KP; ++w) t += red_ss[w][mb][lq];
+      const float rr = rsqrtf(t / K + epi.norm_eps);
+      y = f32x4{y[0] * rr, y[1] * rr, y[2] * rr, y[3] * rr};
+    }
+    if (epi.mode == EPI_PART) {
+      if (row < M) *reinterpret_cast<f32x4*>(epi.part + ((int64_t)sp * M + row) * N + nt * 16 + 4 * g) = y;
+    } else {
+      tile_epilogue(epi, y, EpiPre{}, row, g, nt, M, N);   // EPI_STORE or EPI_SWIGLU: no inputs of their own
+    }
+  }
+}
+
 // ----------------------------------------------------------------------------- fp32 MFMA
 // Unfused fp32 path (row kernels finish the layer), on v_mfma_f32_16x16x4f32 (fp32 products and
 // sums).  A small fp32 model's product is bound by latency, not by bytes (0.25-2 MB of weights
@@ -484,8 +668,28 @@ adt_status launch_pack(const void* const* srcs, const int32_t* rows, int n_src, 
 // the whole K per workgroup where that already gives >= 192 workgroups (O 9.1 us and the
 // draft FC 15.5 at 61 rows), except a long K at > 32 rows, which takes T = 4 with about ten
 // k-tiles per wave per range (down at 61 rows: T = 4 S = 4 20.5 us against 28 at S = 1).
-RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide) {
+// More than 64 rows with the input in the fragment layout (frag): the LDS-staged kernel where it
+// was the faster one at 75, 90 and 122 rows -- wide products of more than three tiles per CU (one
+// workgroup per CU, up to eight tiles; LM head of 16384 x 4096 42-49 -> 31-35 us), and partial
+// sums of a long K: four tiles and four K ranges (7B down), or, for narrow products, two tiles
+// and the K ranges that fill the CUs (LlamaGen-XL down 17.3 -> 8.1 us with six; at K = 1280 the
+// separate finish costs what the split gains).  Two to three tiles per CU: T = 3 in one round of
+// the CUs on the register kernel (QKV 51 -> 32 us at 122 rows, 44 -> 29 at 90).
+RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide, bool frag) {
   const int mt = (M + 15) / 16, tiles = N / 16, KT = K / 32;
+  if (mt > 4 && frag) {
+    if (wide && tiles > 768) {
+      const int g = 256 * ((tiles + 2047) / 2048), t = (tiles + g - 1) / g;
+      return {t <= 4 ? 4 : (t <= 6 ? 6 : 8), 1, g, true};
+    }
+    if (partial && tiles >= 192 && tiles % 4 == 0 && tiles <= 512 && K > 8192)
+      return {4, std::min(4, 1024 / tiles), tiles / 4, true};
+    if (partial && tiles < 192 && K >= 3072) {
+      const int g = (tiles + 1) / 2, s = std::min({GEMM_MAX_SPLITS, 256 / g, KT / 16});
+      if (s >= 2) return {2, s, g, true};
+    }
+  }
+  if (mt > 4 && !partial && tiles > 512 && tiles <= 768) return {3, 1, 256};
   const int tmax = mt <= 4 ? 4 : 2;
   auto ok = [&](int t) { return t <= tmax && tiles % t == 0; };
   if (partial && tiles >= 192 && (mt <= 2 || K <= 8192)) return {1, 1, tiles};
@@ -570,7 +774,7 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
                 ADT_E_ARG, "gemm: the input norm needs one K range");
   // the residual epilogue takes the residual projections' plan, which must keep one K range
   const RowsPlan p = gemm_rows_plan(M, N, K, epi.mode == EPI_PART || epi.mode == EPI_RESID,
-                                    epi.mode == EPI_STORE || epi.mode == EPI_SWIGLU);
+                                    epi.mode == EPI_STORE || epi.mode == EPI_SWIGLU, ldx == X_FRAG);
   ADT_CHECK_ARG(epi.mode != EPI_RESID || p.S == 1, ADT_E_ARG, "gemm: residual epilogue with %d K ranges", p.S);
   ADT_CHECK_ARG(epi.mode != EPI_PART || (size_t)p.S * M * N <= epi.part_elems, ADT_E_CAPACITY,
                 "gemm: %d K-range sums of %d x %d exceed the partial buffer", p.S, M, N);
@@ -597,6 +801,35 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
   } else {                                    \
     ADT_GR_L(MTV, TV, KCV, false, false);     \
   }
+  if (p.dma) {
+#define ADT_GD_L(MTV, TV, RBV, NSTV, NV)                                                                          \
+  hipExtLaunchKernelGGL((gemm_rows_dma_kernel<MTV, TV, RBV, NSTV, NV>), grid, block, 0, st, ev0, ev1, 0, x, w, M, N, \
+                        K, p.S, epi)
+#define ADT_GD(MTV, TV, RBV, NSTV)              \
+  if (epi.norm_eps > 0.f) {                     \
+    ADT_GD_L(MTV, TV, RBV, NSTV, true);         \
+  } else {                                      \
+    ADT_GD_L(MTV, TV, RBV, NSTV, false);        \
+  }
+    // eight row blocks for T = 8 at every row count (75-90 rows: 105-110 against 124 us, whose
+    // six-block stages leave room for two slots only)
+    if (p.T == 8) {
+      ADT_GD(8, 8, 2, 4)
+    } else if (mt <= 6) {
+      if (p.T == 6) { ADT_GD(6, 6, 3, 3) }
+      else if (p.T == 4) { ADT_GD(6, 4, 3, 4) }
+      else ADT_GD_L(6, 2, 3, 4, false);
+    } else {
+      if (p.T == 6) { ADT_GD(8, 6, 2, 5) }
+      else if (p.T == 4) { ADT_GD(8, 4, 2, 5) }
+      else ADT_GD_L(8, 2, 4, 4, false);
+    }
+#undef ADT_GD
+#undef ADT_GD_L
+    ADT_LAUNCH_CHECK();
+    if (splits) *splits = p.S;
+    return ADT_OK;
+  }
   // k-tiles per round: one with three or four tiles (their fragments already keep enough in
   // flight), else two, or three for one row block
 #define ADT_GR_T4(MTV, KCV)              \
@@ -619,7 +852,9 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
     ADT_GR_T6(MTV, KCV)      \
   }
 #define ADT_GR_T2(MTV, KCV)              \
-  if (p.T >= 2) {                        \
+  if (p.T == 3) {                        \
+    ADT_GR(MTV, 3, 1);                   \
+  } else if (p.T == 2) {                 \
     ADT_GR(MTV, 2, KCV);                 \
   } else {                               \
     ADT_GR(MTV, 1, KCV);                 \

@@ -24,7 +24,14 @@ def rt():
     return runtime
 
 
-def _check_verify(rt, cfg, n, seed=0):
+def _check_verify(rt, cfg, n, seed=0, by_row=False):
+    """by_row (wide bf16 models): one unmirrored bf16 rounding is amplified by sums over
+    thousands of columns past the element tolerance, whatever computes it, so each logit row is
+    compared by its 2-norm.  The two sides round at the same eight storage points of a layer
+    (two residual copies, q, k, v, attention output, SwiGLU product, features) and can differ
+    there by one ulp, 2^-8; norms and random projections carry relative 2-norm errors through,
+    so the row error is at most about sqrt(8) 2^-8 = 1.1e-2.  A wrong 16-column tile of the MLP
+    alone would be 4e-2."""
     w = synth.model_weights(cfg)
     om, dm, pre = OracleModel(cfg, w), rt.DeviceModel(cfg, w), synth.prefix_ids(cfg)
     sess, dec = rt.DeviceSession(dm, cfg), Decoder(cfg, om, pre)
@@ -47,6 +54,11 @@ def _check_verify(rt, cfg, n, seed=0):
     lo, hi = cfg.img_lo, cfg.img_hi
     atol, rtol = TOL[cfg.model.dtype]
     err = np.abs(got[:, lo:hi] - ref[:, lo:hi])
+    if by_row:
+        rel = np.linalg.norm(err, axis=1) / np.linalg.norm(ref[:, lo:hi], axis=1)
+        print("row errors", rel.max())
+        assert (rel <= 8 ** 0.5 / 256).all(), rel.max()
+        return
     assert np.isfinite(got[:, lo:hi]).all() and (err <= atol + rtol * np.abs(ref[:, lo:hi])).all(), err.max()
 
 
@@ -56,3 +68,15 @@ def test_verify_f32_odd_shapes(rt, ffn, vocab, n):
     per workgroup."""
     cfg = synth.shrink(synth.get_config("tiny"), ffn=ffn, vocab=vocab)
     _check_verify(rt, cfg, n)
+
+
+@pytest.mark.parametrize("heads,ffn,vocab,n", [(2, 3104, 12544, 65), (2, 3072, 16384, 96), (4, 8224, 24576, 97),
+                                               (4, 8224, 28672, 127), (48, 10240, 1024, 66), (48, 10240, 1024, 128)])
+def test_verify_bf16_65_to_128_rows(rt, heads, ffn, vocab, n):
+    """Five to eight row blocks: the LDS-staged products with four, six and eight column tiles
+    per workgroup (uneven groups among them), K split for narrow and for wide outputs over
+    uneven ranges, and the three-tile QKV."""
+    d = 64 * heads
+    cfg = synth.shrink(synth.get_config("llamagen_xl"), n_layers=1, d_model=d, n_heads=heads, ffn=ffn, vocab=vocab)
+    cfg = dataclasses.replace(cfg, prefix_len=70, img_hi=vocab, prefix_hi=vocab, grid_h=8, grid_w=16)
+    _check_verify(rt, cfg, n, by_row=d > 2048)
