@@ -908,7 +908,7 @@ static int act_blocks(const adt_session_s* s, int rows) { return s->dt == ADT_BF
 static adt_status resid_proj(adt_session_s* s, const void* X, const void* W, int rows, int K, int assign,
                              hipStream_t st) {
   const int dm = s->dm, pk = act_blocks(s, rows);
-  if (gemm_rows_plan(rows, dm, K, true).S == 1) {
+  if (gemm_resid_plan(rows, dm, K).S == 1) {
     GemmEpi e;
     e.mode = EPI_RESID;
     e.resid = s->h;

@@ -198,7 +198,8 @@ __device__ __forceinline__ float sumsq8(bf16x8 v, float s) {
   return s;
 }
 
-// MT = 16-row blocks of M, T = 16-column tiles per workgroup, KC = k-tiles per load round.
+// MT = 16-row blocks per workgroup (row group blockIdx.y takes MT of M's), T = 16-column tiles per
+// workgroup, KC = k-tiles per load round.
 // Workgroup b takes column block b / S and K range b % S; wave w takes the w-th eighth of the
 // range.  Rounds are double-buffered: round r + 1's fragments are requested before round r's
 // MFMAs, so one round stays in flight per wave.  With stagger the wave starts its rounds at an
@@ -212,7 +213,7 @@ __device__ __forceinline__ float sumsq8(bf16x8 v, float s) {
 template <int MT, int T, int KC, bool NORM, bool PRE>
 __global__ __launch_bounds__(TILE_THREADS) void gemm_rows_kernel(const uint16_t* __restrict__ X, int ldx,
                                                                  const uint16_t* __restrict__ Wp, int M, int N, int K,
-                                                                 int S, int stagger, GemmEpi epi) {
+                                                                 int S, GemmEpi epi) {
   constexpr int TT = MT * T;                            // 16x16 output blocks per workgroup
   constexpr int TR = TT < TILE_WAVES ? TT : TILE_WAVES; // blocks finished per LDS round
   constexpr int NR = (TT + TR - 1) / TR;                // rounds
@@ -230,18 +231,18 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_rows_kernel(const uint16_t*
   const int kt0 = ks0 + (int)((int64_t)(ks1 - ks0) * wave / TILE_WAVES);
   const int kt1 = ks0 + (int)((int64_t)(ks1 - ks0) * (wave + 1) / TILE_WAVES);
   const int nk = kt1 - kt0, span = (nk + KC - 1) / KC * KC;
-  const int rot = (stagger && nk > 0) ? (int)((blockIdx.x * 37u) % (unsigned)(span / KC)) * KC : 0;
+  const int rot = nk > 0 ? (int)((blockIdx.x * 37u) % (unsigned)(span / KC)) * KC : 0;
   const bf16x8* wp[T];
 #pragma unroll
   for (int t = 0; t < T; ++t) wp[t] = reinterpret_cast<const bf16x8*>(Wp) + (int64_t)(t0 + min(t, tc - 1)) * KT * 64 + lane;
   // input fragment m of k-tile kk at xp[m] + kk * xks: row-major rows (clamped to M - 1), or
   // the fragment layout's 1 KB blocks (row blocks past the last clamped to it)
-  const int mt = (M + 15) / 16;
+  const int mt = (M + 15) / 16, mb0 = blockIdx.y * MT;
   const uint16_t* xp[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
-    xp[m] = ldx == X_FRAG ? X + ((int64_t)min(m, mt - 1) * WAVE + lane) * 8
-                          : X + (int64_t)min(m * 16 + lq, M - 1) * ldx + g * 8;
+    xp[m] = ldx == X_FRAG ? X + ((int64_t)min(mb0 + m, mt - 1) * WAVE + lane) * 8
+                          : X + (int64_t)min((mb0 + m) * 16 + lq, M - 1) * ldx + g * 8;
   const int64_t xks = ldx == X_FRAG ? (int64_t)mt * WAVE * 8 : 32;
   // round start of the i-th round (c = kt0 + i * KC) after the rotation
   auto kmap = [&](int c) {
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_rows_kernel(const uint16_t*
 #pragma unroll
   for (int r = 0; r < (PRE ? NR : 1); ++r) {
     const int q = r * TR + wave;
-    if (PRE && wave < TR && q < TT && q / MT < tc) pre[r] = epi_preload(epi, (q % MT) * 16 + lq, g, t0 + q / MT, M, N);
+    if (PRE && wave < TR && q < TT && q / MT < tc) pre[r] = epi_preload(epi, (mb0 + q % MT) * 16 + lq, g, t0 + q / MT, M, N);
   }
   f32x4 acc[T][MT];
   float ss[MT];
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_rows_kernel(const uint16_t*
         y = f32x4{y[0] + v[0], y[1] + v[1], y[2] + v[2], y[3] + v[3]};
       }
       const int q = q0 + wave;
-      const int row = (q % MT) * 16 + lq, nt = t0 + q / MT;
+      const int row = (mb0 + q % MT) * 16 + lq, nt = t0 + q / MT;
       if (NORM) {
         float t = 0.f;
 #pragma unroll
@@ -675,7 +676,7 @@ adt_status launch_pack(const void* const* srcs, const int32_t* rows, int n_src, 
 // and the K ranges that fill the CUs (LlamaGen-XL down 17.3 -> 8.1 us with six; at K = 1280 the
 // separate finish costs what the split gains).  Two to three tiles per CU: T = 3 in one round of
 // the CUs on the register kernel (QKV 51 -> 32 us at 122 rows, 44 -> 29 at 90).
-RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide, bool frag) {
+static RowsPlan gemm_rows_plan_all(int M, int N, int K, bool partial, bool wide, bool frag) {
   const int mt = (M + 15) / 16, tiles = N / 16, KT = K / 32;
   if (mt > 4 && frag) {
     if (wide && tiles > 768) {
@@ -729,6 +730,59 @@ RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide, bool frag)
   return {T, S, blocks};
 }
 
+// Row groups.  A product of few tiles at 17-128 rows leaves CUs idle, or (one tile a workgroup) has
+// every workgroup read all M input rows again; what bounds it is how long a wave loads, (T + row
+// blocks) fragments a k-tile.  Workgroups of T tiles and rb < mt row blocks, as many as one round
+// of the CUs takes, load the fewest (a second round costs more than it saves: QKV of 3840 x 1280
+// at 120 rows, T = 1 and rb = 4 in 480 workgroups 14.6 us, T = 2 in 240 9.5); row groups of a
+// column group share its weights in L2.  Ties: the narrower workgroup (1280 x 2560 at 72 rows:
+// T = 1, rb = 2 6.7 us, T = 2, rb = 1 7.8), but one row block where its whole K range is one round
+// of loads (1280 x 1280: T = 2, rb = 1 5.1 us, T = 1, rb = 2 5.5).  T = 3 and 6 were no faster
+// (6 at 122 rows: 46 against 33 us for QKV of 12288 x 4096).  All rows per workgroup -> row groups:
+//   1280 x 1280  24 / 61 / 72 / 120 rows  5.4 -> 4.2, 7.0 -> 5.0, 8.0 -> 5.1, 9.4 -> 6.2 us
+//   1280 x 3584  24 / 40 / 61 rows  8.7 -> 6.9, 10.6 -> 6.8, 11.7 -> 8.6
+//   3840 x 1280  61 / 90 / 122 rows  8.5 -> 7.5, 10.5 -> 8.5, 11.8 -> 9.8
+//   7168 x 1280  90 / 122 rows  12.3 -> 10.7, 14.1 -> 11.7;  8192 x 4096  122 rows  26.6 -> 24.0
+//   4096 x 4096  61 / 90 / 122 rows  13.7 -> 12.6, 17.2 -> 15.3, 20.3 -> 16.5
+// T = 0 where all rows per workgroup (load of `all` fragments) is as good.
+static RowsPlan row_group_plan(int mt, int tiles, int KT, int all) {
+  RowsPlan p{0, 1, 0};
+  auto take = [&](int t, int rb) {
+    const int g = (tiles + t - 1) / t;
+    if (rb >= mt || t + rb >= all || g * ((mt + rb - 1) / rb) > 256) return;
+    all = t + rb;
+    p = {t, 1, g};
+    p.rb = rb;
+  };
+  if (KT <= 5 * TILE_WAVES) {
+    for (int rb = 1; rb <= 4; ++rb)
+      for (int t : {1, 2, 4}) take(t, rb);
+  } else {
+    for (int t : {1, 2, 4})
+      for (int rb = 1; rb <= 4; ++rb) take(t, rb);
+  }
+  return p;
+}
+
+RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide, bool frag) {
+  const RowsPlan p = gemm_rows_plan_all(M, N, K, partial, wide, frag);
+  const int mt = (M + 15) / 16;
+  if (p.S > 1 || mt == 1) return p;
+  const RowsPlan r = row_group_plan(mt, N / 16, K / 32, p.T + mt);
+  return r.T ? r : p;
+}
+
+// Narrow products in row groups also where K-range sums are the faster product: their finish is a
+// launch of its own (1280 x 3584 at 90 rows: 8.4 us against 6.7 and 4.2; 120 rows: 9.8 against 7.8 and 4.2).
+RowsPlan gemm_resid_plan(int M, int N, int K) {
+  const int mt = (M + 15) / 16;
+  if (mt > 1 && N / 16 < 192) {
+    const RowsPlan r = row_group_plan(mt, N / 16, K / 32, 1 + mt);
+    if (r.T) return r;
+  }
+  return gemm_rows_plan(M, N, K, true);
+}
+
 adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int K, int dtype, float* part,
                        const GemmEpi& epi, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int* splits) {
   ADT_CHECK_ARG(M >= 1 && M <= 128, ADT_E_CAPACITY, "gemm: M=%d outside [1,128]", M);
@@ -772,23 +826,25 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
   }
   ADT_CHECK_ARG(epi.norm_eps == 0.f || (epi.norm_eps > 0.f && epi.mode != EPI_PART && epi.mode != EPI_RESID),
                 ADT_E_ARG, "gemm: the input norm needs one K range");
-  // the residual epilogue takes the residual projections' plan, which must keep one K range
-  const RowsPlan p = gemm_rows_plan(M, N, K, epi.mode == EPI_PART || epi.mode == EPI_RESID,
-                                    epi.mode == EPI_STORE || epi.mode == EPI_SWIGLU, ldx == X_FRAG);
+  // the residual epilogue's plan must keep one K range
+  const RowsPlan p = epi.mode == EPI_RESID ? gemm_resid_plan(M, N, K)
+                                           : gemm_rows_plan(M, N, K, epi.mode == EPI_PART,
+                                                            epi.mode == EPI_STORE || epi.mode == EPI_SWIGLU, ldx == X_FRAG);
   ADT_CHECK_ARG(epi.mode != EPI_RESID || p.S == 1, ADT_E_ARG, "gemm: residual epilogue with %d K ranges", p.S);
   ADT_CHECK_ARG(epi.mode != EPI_PART || (size_t)p.S * M * N <= epi.part_elems, ADT_E_CAPACITY,
                 "gemm: %d K-range sums of %d x %d exceed the partial buffer", p.S, M, N);
   const int mt = (M + 15) / 16, KT = K / 32;
-  const int stagger = 1;
-  const dim3 grid(p.G * p.S), block(TILE_THREADS);
+  // row blocks per workgroup: all of them, or (p.rb > 0) row groups of p.rb in the grid's second dimension
+  const int mg = p.rb ? p.rb : mt;
+  const dim3 grid(p.G * p.S, (mt + mg - 1) / mg), block(TILE_THREADS);
   const uint16_t* x = (const uint16_t*)X;
   const uint16_t* w = (const uint16_t*)Wp;
   // epilogue inputs requested early for QKV and the residual epilogue (not at > 4 row blocks,
   // where the registers are taken by the accumulators)
-  const bool pre = (epi.mode == EPI_QKV || epi.mode == EPI_RESID) && mt <= 4;
+  const bool pre = (epi.mode == EPI_QKV || epi.mode == EPI_RESID) && mg <= 4;
 #define ADT_GR_L(MTV, TV, KCV, NV, PV)                                                                            \
   hipExtLaunchKernelGGL(gemm_rows_kernel<MTV, TV, KCV, NV, (PV && MTV <= 4)>, grid, block, 0, st, ev0, ev1, 0, x, \
-                        ldx, w, M, N, K, p.S, stagger, epi)
+                        ldx, w, M, N, K, p.S, epi)
 #define ADT_GR(MTV, TV, KCV)                  \
   if (epi.norm_eps > 0.f) {                   \
     if (pre && MTV <= 4) {                    \
@@ -862,7 +918,7 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
   // k-tiles per round: at one row block 3, or the wave's whole K range when that is at most
   // five k-tiles (one round trip: LlamaGen-XL O at 11 rows 4.5 against 4.85 us)
   const bool one_round = (KT + p.S * TILE_WAVES - 1) / (p.S * TILE_WAVES) <= 5;
-  switch (mt) {
+  switch (mg) {
     case 1:
       if (one_round) {
         ADT_GR_T6(1, 5)

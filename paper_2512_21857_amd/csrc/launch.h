@@ -101,8 +101,11 @@ struct RowsPlan {
   int T, S;       // at most T 16-column tiles per workgroup, S K ranges
   int G;          // column groups: group c takes tiles [c tiles / G, (c + 1) tiles / G)
   bool dma = false;   // the LDS-staged kernel (more than 64 rows, input in the fragment layout)
+  int rb = 0;         // > 0: workgroups take rb 16-row blocks each, row groups side by side (at most 4)
 };
 RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide = false, bool frag = true);
+// The plan of a residual projection; S = 1: EPI_RESID, else EPI_PART and the finish by row kernels.
+RowsPlan gemm_resid_plan(int M, int N, int K);
 constexpr int GEMM_MAX_SPLITS = 8;
 // fp32: part[M][N] = X . W^T (consumed by the row kernels).  bf16: the kernel above with the
 // epilogue epi; *splits (if given) gets S.  bf16 X is row-major with leading dimension ldx, or

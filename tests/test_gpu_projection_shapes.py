@@ -80,3 +80,14 @@ def test_verify_bf16_65_to_128_rows(rt, heads, ffn, vocab, n):
     cfg = synth.shrink(synth.get_config("llamagen_xl"), n_layers=1, d_model=d, n_heads=heads, ffn=ffn, vocab=vocab)
     cfg = dataclasses.replace(cfg, prefix_len=70, img_hi=vocab, prefix_hi=vocab, grid_h=8, grid_w=16)
     _check_verify(rt, cfg, n, by_row=d > 2048)
+
+
+@pytest.mark.parametrize("heads,ffn,n", [(2, 96, 17), (2, 96, 50), (20, 3584, 33), (20, 3584, 61), (20, 3584, 90),
+                                         (20, 3584, 113)])
+def test_verify_bf16_row_groups(rt, heads, ffn, n):
+    """Products whose workgroups take one to four of the two to eight row blocks: row groups that
+    do not divide the blocks, column groups that do not divide the tiles."""
+    d = 64 * heads
+    cfg = synth.shrink(synth.get_config("llamagen_xl"), n_layers=2, d_model=d, n_heads=heads, ffn=ffn, vocab=2064)
+    cfg = dataclasses.replace(cfg, prefix_len=70, img_hi=2064, prefix_hi=2064, grid_h=8, grid_w=16)
+    _check_verify(rt, cfg, n, by_row=d > 1024)
