@@ -553,6 +553,7 @@ struct adt_session_s {
   float *top_val, *lse;
   void* attn_ws;
   size_t attn_ws_bytes;
+  uint32_t* attn_arrived;   // [nb * H]
   void* topk_ws;          // per-chunk candidates of the expansions' top-k
   size_t topk_ws_bytes;
   void* acc_ws;
@@ -677,6 +678,7 @@ static size_t session_layout(adt_session_s* s, char* base) {
   s->rope = b.take<float2>((size_t)s->d.s_cap * (s->Dh / 2));
   s->attn_ws_bytes = tree_attn_ws_bytes(s->nb, s->H, s->Dh, R / s->nb, s->d.s_cap, s->dt);
   s->attn_ws = b.take<char>(std::max<size_t>(s->attn_ws_bytes, 256));
+  s->attn_arrived = b.take<uint32_t>((size_t)s->nb * s->H);
   s->acc_ws_bytes = adt_accept_workspace_size(s->V);
   s->acc_ws = b.take<char>(s->acc_ws_bytes);
   s->topk_ws_bytes = row_topk_ws_bytes(R, 16);
@@ -764,6 +766,7 @@ extern "C" adt_status adt_session_create(const adt_model* m, const adt_session_d
   hipError_t he = hipHostMalloc((void**)&s->h_acc, sizeof(int32_t) * (2 * R + 2), hipHostMallocDefault);
   if (he == hipSuccess)
     he = hipMemcpy(s->allowed_img, s->allowed_h.data(), sizeof(int32_t) * 2 * s->T, hipMemcpyHostToDevice);
+  if (he == hipSuccess) he = hipMemsetAsync(s->attn_arrived, 0, sizeof(uint32_t) * s->nb * s->H, nullptr);
   if (he == hipSuccess && launch_rope_table(s->rope, s->d.s_cap, s->Dh, m->d.rope_theta, nullptr) == ADT_OK)
     he = hipDeviceSynchronize();
   if (he != hipSuccess) {
@@ -952,7 +955,8 @@ static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t*
     rl.o_pk = pk;
     TRY(launch_tree_attn(s->q, kc, vc, cache_sb, stride_h, s->scal + SC_KV, s->scal + SC_NQ, s->scal + SC_TAIL, mask,
                          rl, nb, H, Dh, M, s->d.s_cap, scale, dt, s->att, s->attn_ws,
-                         s->attn_ws_bytes, st, e >= 0 ? g_prof.ev[e] : nullptr, e >= 0 ? g_prof.ev[e + 1] : nullptr));
+                         s->attn_ws_bytes, st, e >= 0 ? g_prof.ev[e] : nullptr, e >= 0 ? g_prof.ev[e + 1] : nullptr,
+                         s->attn_arrived));
     prof_done(e, ADT_PROF_ATTN, nb * (2.0 * L_pre * H * Dh * es + 4.0 * M * H * Dh * es) + 16.0 * M,
               4.0 * rows * (L_pre + n_tail) * H * Dh);
     return ADT_OK;

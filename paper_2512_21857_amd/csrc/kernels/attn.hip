@@ -28,6 +28,9 @@ constexpr int ATT_MAX_SPLITS = 64;
 // weights of masked keys (-inf) come out 0 without a test, and split partials that saw no key
 // carry weight 0 in the merge.
 constexpr float ATT_M_FLOOR = -1e30f;
+// With the merge in the same launch, key blocks a split takes at the least: a short prefix stays in
+// one split and needs no merge.
+constexpr int ATT_MIN_BLOCKS = 2;
 
 __device__ __forceinline__ bool tail_visible(uint64_t w0, uint64_t w1, int j) {
   const uint64_t w = j < 64 ? w0 : w1;
@@ -46,6 +49,16 @@ __device__ __forceinline__ bool key_visible(int key, int k_end, int L, uint64_t 
 // 2^x on the transcendental unit alone (no denormal fix-up: softmax weights that small
 // are zero for every purpose here).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Two floats written through to, or read from, the point where the device's XCDs see the same memory.
+__device__ __forceinline__ void agent_store2(float* p, float a, float b) {
+  const uint64_t v = (uint64_t)__float_as_uint(b) << 32 | __float_as_uint(a);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 agent_load2(const float* p) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
 
 // The work-balanced sequence order (defined with the shared-block kernel below).
 __device__ int balanced_seq(int y, int B, const int32_t* kv_len, const int32_t* n_q, const int32_t* n_tail,
@@ -476,7 +489,7 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
     int64_t stride_b, int64_t stride_h, const int32_t* __restrict__ kv_len, const int32_t* __restrict__ n_q,
     const int32_t* __restrict__ n_tail, const uint64_t* __restrict__ mask, AttnRows rl, int H, int nq_max,
     int kv_cap, float scale_log2, uint16_t* __restrict__ out, int splits, float* __restrict__ part_o,
-    float* __restrict__ part_ml) {
+    float* __restrict__ part_ml, uint32_t* __restrict__ arrived) {
   constexpr int BLK_KT = KH == 4 ? 128 : 64;      // keys per block: 32 per wave and half-step
   constexpr int CH = DH / 8;                     // 16-byte chunks per row
   constexpr int DT = DH / 16, KS = DH / 32;
@@ -503,8 +516,11 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
   // with splits > 1, split sp takes a contiguous share of the live blocks (balanced on the
   // device, so a replayed launch follows the growing prefix)
   const int nblk_all = (total + BLK_KT - 1) / BLK_KT;
-  const int per = (nblk_all + splits - 1) / splits;
+  const int even = (nblk_all + splits - 1) / splits, per = arrived ? max(even, ATT_MIN_BLOCKS) : even;
   const int blk0 = min(nblk_all, sp * per), nblk = min(nblk_all, blk0 + per);
+  // splits with keys; without `arrived` the empty ones store empty partials for the merge launch
+  const int live = arrived ? max(1, (nblk_all + per - 1) / per) : splits;
+  if (sp >= live) return;
   const uint16_t* kbase = kc + b * stride_b + h * stride_h;
   const uint16_t* vbase = vc + b * stride_b + h * stride_h;
 
@@ -691,12 +707,20 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
     }
   }
   if (active && kpart == 0 && qr < nq) {
-    if (splits == 1) {
+    if (live == 1) {
       const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
       for (int d = 0; d < DT; ++d)
         store4(out + rl.o_index(b, qr, H, DH, h, d * 16 + 4 * g), o[d][0] * inv, o[d][1] * inv, o[d][2] * inv,
                o[d][3] * inv);
+    } else if (P > 1 && arrived) {
+      const int64_t pr = (((int64_t)b * H + h) * splits + sp) * nq_max + qr;
+#pragma unroll
+      for (int d = 0; d < DT; ++d) {
+        agent_store2(part_o + pr * DH + d * 16 + 4 * g, o[d][0], o[d][1]);
+        agent_store2(part_o + pr * DH + d * 16 + 4 * g + 2, o[d][2], o[d][3]);
+      }
+      if (g == 0) agent_store2(part_ml + pr * 2, m_run, l_run);
     } else {
       // this split's (O, m, l) for the log-sum-exp merge (m in the log2 domain)
       const int64_t pr = (((int64_t)b * H + h) * splits + sp) * nq_max + qr;
@@ -706,6 +730,52 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
         part_ml[pr * 2] = m_run;
         part_ml[pr * 2 + 1] = l_run;
       }
+    }
+  }
+  // The last split of the pair to get here merges them all, in split order, four dims of one
+  // query a thread: the partials of a split are complete at the agent's coherence point (write-
+  // through stores, waited for) before its arrival counts, and are read past the local caches.
+  if constexpr (P > 1) {
+    if (!arrived || live == 1) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();   // (and the merge area of the key parts has been read)
+    uint32_t* last = reinterpret_cast<uint32_t*>(smem);
+    uint32_t* cnt = arrived + b * H + h;
+    if (threadIdx.x == 0) *last = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    __syncthreads();
+    if (*last != (uint32_t)live) return;
+    if (threadIdx.x == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    const int64_t base = ((int64_t)b * H + h) * splits * nq_max;
+    for (int i = threadIdx.x; i < nq * (DH / 4); i += NW * WAVE) {
+      const int row = i / (DH / 4), d = i % (DH / 4) * 4;
+      float M = ATT_M_FLOOR, ls = 0.f;
+      float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int s0 = 0; s0 < live; s0 += 8) {   // eight splits in flight
+        float2 ml[8], lo[8], hi[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int64_t r = base + (int64_t)min(s0 + j, live - 1) * nq_max + row;
+          ml[j] = agent_load2(part_ml + r * 2);
+          lo[j] = agent_load2(part_o + r * DH + d);
+          hi[j] = agent_load2(part_o + r * DH + d + 2);
+        }
+        float Mn = M;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) Mn = fmaxf(Mn, ml[j].x);
+        const float a = fast_exp2(M - Mn);
+        ls *= a;
+        acc = make_float4(acc.x * a, acc.y * a, acc.z * a, acc.w * a);
+        M = Mn;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (s0 + j >= live) continue;
+          const float w = fast_exp2(ml[j].x - M);
+          ls += w * ml[j].y;
+          acc = make_float4(acc.x + w * lo[j].x, acc.y + w * lo[j].y, acc.z + w * hi[j].x, acc.w + w * hi[j].y);
+        }
+      }
+      const float inv = ls > 0.f ? 1.f / ls : 0.f;
+      store4(out + rl.o_index(b, row, H, DH, h, d), acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
     }
   }
 }
@@ -750,7 +820,7 @@ size_t tree_attn_ws_need(int B, int H, int Dh, int nq_max, int kv_cap, int dtype
 static adt_status attn_bf16(const void* q, const void* k, const void* v, int64_t sb, int64_t sh, const int32_t* kv_len,
                             const int32_t* n_q, const int32_t* n_tail, const uint64_t* mask, AttnRows rl, int B, int H, int Dh,
                             int nq_max, int kv_cap, float scale, void* out, void* ws, size_t ws_bytes, hipStream_t st,
-                            hipEvent_t ev0, hipEvent_t ev1) {
+                            hipEvent_t ev0, hipEvent_t ev1, uint32_t* arrived) {
   const float sl2 = scale * LOG2E;
   if (attn_use_wg(B, H, nq_max)) {
     const dim3 grid(B * H);
@@ -782,11 +852,12 @@ static adt_status attn_bf16(const void* q, const void* k, const void* v, int64_t
   }
   const dim3 grid(H, B, S);
   const int qt = (nq_max + 15) / 16;
-  hipEvent_t e1 = S > 1 ? nullptr : ev1;
+  const bool merge = S > 1 && !arrived;   // partials merged by a launch of its own
+  hipEvent_t e1 = merge ? nullptr : ev1;
 #define ADT_ATTN_BLK_P(DHV, KHV, NWV, PV)                                                                       \
   hipExtLaunchKernelGGL(tree_attn_blk_kernel<DHV, KHV, NWV, PV>, grid, dim3(NWV * WAVE), 0, st, ev0, e1, 0,        \
                         (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, sb, sh, kv_len, n_q, n_tail,   \
-                        mask, rl, H, nq_max, kv_cap, sl2, (uint16_t*)out, S, part_o, part_ml)
+                        mask, rl, H, nq_max, kv_cap, sl2, (uint16_t*)out, S, part_o, part_ml, S > 1 ? arrived : nullptr)
   // a split workgroup owns the CU and streams a few blocks, so it keeps three in flight; many
   // pairs without splits keep one (two workgroups share a CU)
 #define ADT_ATTN_BLK(DHV, KHV, NWV)        \
@@ -810,7 +881,7 @@ static adt_status attn_bf16(const void* q, const void* k, const void* v, int64_t
 #undef ADT_ATTN_BLK
 #undef ADT_ATTN_BLK_P
   ADT_LAUNCH_CHECK();
-  if (S > 1) {
+  if (merge) {
     const int qpb = COMB_THREADS / (Dh / 4);
     const dim3 g2((nq_max + qpb - 1) / qpb, H, B);
     hipExtLaunchKernelGGL(tree_attn_combine_kernel, g2, dim3(COMB_THREADS), 0, st, nullptr, ev1, 0, part_o, part_ml,
@@ -823,7 +894,7 @@ static adt_status attn_bf16(const void* q, const void* k, const void* v, int64_t
 adt_status launch_tree_attn(const void* q, const void* k, const void* v, int64_t sb, int64_t sh, const int32_t* kv_len,
                             const int32_t* n_q, const int32_t* n_tail, const uint64_t* mask, AttnRows rl, int B, int H, int Dh,
                             int nq_max, int kv_cap, float scale, int dtype, void* out, void* ws, size_t ws_bytes,
-                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, uint32_t* arrived) {
   ADT_CHECK_ARG(rl.o_pk == 0 || (dtype == ADT_BF16 && (H * Dh) % 32 == 0 && !rl.row_off &&
                                   (int64_t)(B - 1) * rl.rs_b + (int64_t)(nq_max - 1) * rl.rs_i < 16LL * rl.o_pk),
                 ADT_E_ARG, "tree_attn: fragment-layout output of %d row blocks (bf16, rows of a multiple of 32 values)",
@@ -839,7 +910,7 @@ adt_status launch_tree_attn(const void* q, const void* k, const void* v, int64_t
     return ADT_OK;
   }
   return attn_bf16(q, k, v, sb, sh, kv_len, n_q, n_tail, mask, rl, B, H, Dh, nq_max, kv_cap, scale, out, ws, ws_bytes,
-                   st, ev0, ev1);
+                   st, ev0, ev1, arrived);
 }
 
 }  // namespace adt

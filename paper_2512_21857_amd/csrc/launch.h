@@ -50,7 +50,10 @@ size_t tree_attn_ws_need(int B, int H, int Dh, int nq_max, int kv_cap, int dtype
 adt_status launch_tree_attn(const void* q, const void* k, const void* v, int64_t sb, int64_t sh, const int32_t* kv_len,
                             const int32_t* n_q, const int32_t* n_tail, const uint64_t* mask, AttnRows rl, int B, int H,
                             int Dh, int nq_max, int kv_cap, float scale, int dtype, void* out, void* ws,
-                            size_t ws_bytes, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                            size_t ws_bytes, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                            uint32_t* arrived = nullptr);
+// (arrived: B * H counters, zero before the first launch that gets them and left zero by every
+// one, for launches that follow one another in stream order: key splits merge in the same launch.)
 
 // gemm.hip
 size_t packed_bytes(int total_rows, int K, int dtype);
