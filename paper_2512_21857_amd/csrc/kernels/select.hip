@@ -1,8 +1,8 @@
 // Draft-tree expansion and greedy acceptance (Sec. 3.1; Sec. 4.2, Eq. 3-5).
 //
 // row_topk: per logits row, over its allowed id range, the top-k ids ordered by
-//   (logit desc, id asc) and the log-sum-exp; one workgroup per row.  Each thread keeps a
-//   sorted private list over a strided slice, then k rounds of a block-wide argmax merge.
+//   (logit desc, id asc) and the log-sum-exp, in two stages (2048-id chunks, then rows) of
+//   sorted lists whose largest head is taken k times.
 // expand_level: children of the frontier rows (score = parent score + logit - lse, i.e. the
 //   log of the product of confidences of Eq. 3), appended to the candidate pool, and the
 //   next frontier (top-k of the new layer by (score desc, creation asc)); it also lays out
@@ -19,16 +19,13 @@ constexpr int SEL_THREADS = 256;
 
 ADT_DEVICE_ERROR_WORD(select)
 
-__device__ __forceinline__ bool better(float a, int ia, float b, int ib) { return a > b || (a == b && ia < ib); }
-
 constexpr int TOPK_THREADS = 256;
 constexpr int TOPK_WAVES = TOPK_THREADS / WAVE;
 constexpr int TOPK_CHUNK = 8 * TOPK_THREADS;   // logits per chunk workgroup (two float4 per thread)
 constexpr int TOPK_MAX_CHUNKS = 32;            // vocabularies up to 65536
 
 // (value desc, id asc) as one 64-bit key, larger = better: the value's bits made
-// order-preserving (-0 taken as +0) above the id's complement.  For values that are not NaN
-// this is the order of better().
+// order-preserving (-0 taken as +0) above the id's complement.
 __device__ __forceinline__ uint64_t best_key(float v, int id) {
   const uint32_t u = __float_as_uint(v + 0.f);
   const uint32_t o = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -59,61 +56,37 @@ __device__ __forceinline__ uint64_t wave_max_key(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Wave-wide argmax of (value desc, id asc) over every lane's (v, id), none NaN: v and id
-// become the winner's (v exactly as the lane held it) and owner the lowest lane holding it.
-__device__ __forceinline__ void wave_best(float& v, int& id, int& owner) {
-  const uint64_t key = best_key(v, id);
-  const uint64_t top = wave_max_key(key);
-  owner = __ffsll((long long)__ballot(key == top)) - 1;
-  v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), owner));
-  id = (int)(0xFFFFFFFFu - (uint32_t)top);
+// The key of a candidate, 0 (below every key) for -inf and NaN, which are never selected.
+__device__ __forceinline__ uint64_t cand_key(float v, int id) { return v > -INFINITY ? best_key(v, id) : 0ull; }
+__device__ __forceinline__ float key_value(uint64_t key) {
+  const uint32_t o = (uint32_t)(key >> 32);
+  return key ? __uint_as_float((o & 0x80000000u) ? (o & 0x7FFFFFFFu) : ~o) : -INFINITY;
 }
+__device__ __forceinline__ int key_id(uint64_t key) { return key ? (int)(0xFFFFFFFFu - (uint32_t)key) : 0x7FFFFFFF; }
 
-// k rounds of "best remaining value of each lane, then the wave's best" over N values per
-// lane (vals / ids, consumed); round q's winner goes to out_v[q] / out_i[q] (from lane 0).
-// Rounds past the live values give (-inf, 0x7FFFFFFF).
-template <int N>
-__device__ __forceinline__ void wave_select(float (&vals)[N], int (&ids)[N], int kk, float* out_v, int* out_i) {
-  const int lane = threadIdx.x % WAVE;
-  for (int q = 0; q < kk; ++q) {
-    float bv = -INFINITY;
-    int bi = 0x7FFFFFFF;
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-      if (better(vals[j], ids[j], bv, bi)) {
-        bv = vals[j];
-        bi = ids[j];
-      }
-    if (bv == -INFINITY) bi = 0x7FFFFFFF;
-    int bl = lane;
-    wave_best(bv, bi, bl);
-    if (lane == bl && bi != 0x7FFFFFFF) {
-#pragma unroll
-      for (int j = 0; j < N; ++j)
-        if (ids[j] == bi) vals[j] = -INFINITY;
-    }
-    if (lane == 0) {
-      out_v[q] = bv;
-      out_i[q] = bi;
-    }
-  }
+// The larger key to a, the smaller to b.
+__device__ __forceinline__ void key_order(uint64_t& a, uint64_t& b) {
+  const bool sw = b > a;
+  const uint64_t t = sw ? b : a;
+  b = sw ? a : b;
+  a = t;
 }
 
 // Top-k ids by (logit desc, id asc) over the allowed range [lo, hi) of each row, and the
 // row's log-sum-exp, in two launches.  Stage 1, one workgroup per (2048-logit chunk, row):
-// the chunk's per-wave (max, sum of exp) pairs and its own top-k (each wave selects from its
-// 512 logits, wave 0 merges the four lists).  Stage 2, one wave per row: the row's top-k
-// from the chunks' lists and the log-sum-exp from their pairs.  Spreading a row over
-// V / 2048 workgroups keeps the selection rounds (k of them, each a scan and a shuffle
-// argmax) short; one workgroup per row ran them over 64 values per lane on a few CUs.
+// every wave's (max, sum of exp) pair and its sorted top-k of its 512 logits.  Stage 2, one
+// workgroup per row: the row's top-k from the wave lists and the log-sum-exp from the pairs.
+// Both stages are a chain of k rounds "the largest head of 64 sorted lists, then pop that
+// list", about 250 clocks a round (the wave maximum by DPP); a lane sorts its eight logits once
+// with a 19-exchange network, so a round looks at one key per lane instead of eight, and the
+// waves' lists go to stage 2 unmerged.  With a scan of eight values a lane and round, and a merge
+// per chunk, 16384 ids (one row, k = 10) had taken 12.2 + 7.4 us; one-row draft of LlamaGen-XL 83.0 -> 72.6 us with it and the
+// merged attention, Lumina's (65536 ids) 221 -> 213.
 template <int KMAX>
 __global__ __launch_bounds__(TOPK_THREADS) void topk_chunk_kernel(const float* __restrict__ logits, int64_t ld, int V,
                                                                   const int32_t* __restrict__ allowed, int ulo,
-                                                                  int uhi, int k, float* __restrict__ cand_v,
-                                                                  int* __restrict__ cand_i,
+                                                                  int uhi, int k, uint64_t* __restrict__ cand,
                                                                   float2* __restrict__ cand_ms, int c0) {
-  __shared__ float wv[TOPK_WAVES][KMAX];
-  __shared__ int wi[TOPK_WAVES][KMAX];
   // workgroup x covers chunk c0 + x of the row (outputs at x)
   const int chunk = blockIdx.x, G = gridDim.x, row = blockIdx.y;
   const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
@@ -122,7 +95,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_chunk_kernel(const float* _
   const float* x = logits + (int64_t)row * ld;
   const bool vec = ((ld & 3) == 0);
   float r[8];
-  int id[8];
+  uint64_t key[8];
+  float m = -INFINITY;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int base = (c0 + chunk) * TOPK_CHUNK + j * 4 * TOPK_THREADS + 4 * tid;
@@ -138,12 +112,11 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_chunk_kernel(const float* _
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      id[4 * j + e] = base + e;
       if (base + e < lo || base + e >= hi) r[4 * j + e] = -INFINITY;
+      key[4 * j + e] = cand_key(r[4 * j + e], base + e);
     }
   }
   // the wave's (max, sum of exp) pair
-  float m = -INFINITY;
 #pragma unroll
   for (int j = 0; j < 8; ++j) m = fmaxf(m, r[j]);
   const float M = wave_max(m);
@@ -154,80 +127,110 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_chunk_kernel(const float* _
   }
   const float S = wave_sum(sacc);
   if (lane == 0) cand_ms[((int64_t)row * G + chunk) * TOPK_WAVES + wave] = make_float2(M, S);
-  const int kk = min(k, hi - lo);
-  wave_select(r, id, kk, wv[wave], wi[wave]);
-  __syncthreads();
-  if (wave != 0) return;
-  // wave 0: the chunk's top-k from the four wave lists (lane w < 4 offers list w's head)
-  float* ov = cand_v + ((int64_t)row * G + chunk) * KMAX;
-  int* oi = cand_i + ((int64_t)row * G + chunk) * KMAX;
-  int h = 0;
-  for (int q = 0; q < kk; ++q) {
-    float hv = -INFINITY;
-    int hid = 0x7FFFFFFF;
-    if (lane < TOPK_WAVES && h < kk) {
-      hv = wv[lane][h];
-      hid = wi[lane][h];
+  if constexpr (KMAX == 1) {   // one key per chunk
+    __shared__ uint64_t wk[TOPK_WAVES];
+    uint64_t best = key[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) best = key[j] > best ? key[j] : best;
+    best = wave_max_key(best);
+    if (lane == 0) wk[wave] = best;
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+      for (int w = 1; w < TOPK_WAVES; ++w) best = wk[w] > best ? wk[w] : best;
+      cand[(int64_t)row * G + chunk] = best;
     }
-    int bl = lane;
-    wave_best(hv, hid, bl);
-    if (lane == bl) ++h;
-    if (lane == 0) {
-      ov[q] = hv;
-      oi[q] = hid;
+  } else {
+    // Batcher's odd-even merge sort of eight
+    constexpr int CA[19] = {0, 2, 4, 6, 0, 1, 4, 5, 1, 5, 0, 1, 2, 3, 2, 3, 1, 3, 5};
+    constexpr int CB[19] = {1, 3, 5, 7, 2, 3, 6, 7, 2, 6, 4, 5, 6, 7, 4, 5, 2, 4, 6};
+#pragma unroll
+    for (int i = 0; i < 19; ++i) key_order(key[CA[i]], key[CB[i]]);
+    const int kk = min(k, hi - lo);
+    uint64_t mine = 0;
+    for (int q = 0; q < kk; ++q) {
+      const uint64_t top = wave_max_key(key[0]);
+      if (lane == q) mine = top;
+      if (key[0] == top) {   // keys are distinct; where none is left, all are 0 and stay so
+#pragma unroll
+        for (int j = 0; j < 7; ++j) key[j] = key[j + 1];
+        key[7] = 0;
+      }
     }
+    if (lane < kk) cand[(((int64_t)row * G + chunk) * TOPK_WAVES + wave) * KMAX + lane] = mine;
   }
 }
 
-// Stage 2: one wave per row over the G chunk lists (G * KMAX <= 8 * WAVE candidates).
+// Stage 2: the G chunks' sorted lists (TOPK_WAVES each, or with KMAX = 1 one key) through LDS; wave 0
+// selects, two lists a lane, the other waves' first sums the pairs, in pair order within the lane.
 template <int KMAX>
-__global__ __launch_bounds__(WAVE) void topk_merge_kernel(const float* __restrict__ cand_v,
-                                                          const int* __restrict__ cand_i,
-                                                          const float2* __restrict__ cand_ms, int G, int V,
-                                                          const int32_t* __restrict__ allowed, int ulo, int uhi,
-                                                          int k, int32_t* __restrict__ top_id, float* __restrict__ top_val,
-                                                          float* __restrict__ lse) {
-  constexpr int N = TOPK_MAX_CHUNKS * KMAX / WAVE > 0 ? TOPK_MAX_CHUNKS * KMAX / WAVE : 1;
-  const int row = blockIdx.x, lane = threadIdx.x;
+__global__ __launch_bounds__(TOPK_THREADS) void topk_merge_kernel(const uint64_t* __restrict__ cand,
+                                                                  const float2* __restrict__ cand_ms, int G, int V,
+                                                                  const int32_t* __restrict__ allowed, int ulo,
+                                                                  int uhi, int k, int32_t* __restrict__ top_id,
+                                                                  float* __restrict__ top_val, float* __restrict__ lse) {
+  constexpr int LISTS = KMAX == 1 ? 1 : TOPK_WAVES, MAXL = TOPK_MAX_CHUNKS * LISTS;
+  constexpr int PAIRS = TOPK_MAX_CHUNKS * TOPK_WAVES / WAVE;
+  static_assert(MAXL <= 2 * WAVE, "two lists a lane");
+  __shared__ uint64_t list[MAXL * KMAX];
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid % WAVE;
   const int lo = max(0, min(allowed ? allowed[row * 2] : ulo, V));
   const int hi = max(lo, min(allowed ? allowed[row * 2 + 1] : uhi, V));
-  const int kk = min(k, hi - lo);
-  // chunk c's list holds its min(k, live) entries; the rest of a list is never read
-  float vals[N];
-  int ids[N];
+  const int kk = min(k, hi - lo), nl = G * LISTS;
+  // a list holds min(k, live) entries; the rest of it was not written
+  for (int e = tid; e < nl * KMAX; e += TOPK_THREADS)
+    list[e] = e % KMAX < kk ? cand[(int64_t)row * nl * KMAX + e] : 0;
+  if (tid / WAVE == 1) {
+    float pm[PAIRS], ps[PAIRS];
+    float gm = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < N; ++j) {
-    const int e = j * WAVE + lane, c = e / KMAX, q = e % KMAX;
-    vals[j] = -INFINITY;
-    ids[j] = 0x7FFFFFFF;
-    if (c < G && q < kk) {
-      vals[j] = cand_v[((int64_t)row * G) * KMAX + e];
-      ids[j] = cand_i[((int64_t)row * G) * KMAX + e];
+    for (int j = 0; j < PAIRS; ++j) {
+      const int e = j * WAVE + lane;
+      pm[j] = -INFINITY;
+      ps[j] = 0.f;
+      if (e < G * TOPK_WAVES) {
+        const float2 p = cand_ms[(int64_t)row * G * TOPK_WAVES + e];
+        pm[j] = p.x;
+        ps[j] = p.y;
+      }
+      gm = fmaxf(gm, pm[j]);
     }
-  }
-  // log-sum-exp from the G * 4 (max, sum) pairs, in pair order within the lane
-  float pm[2 * TOPK_MAX_CHUNKS * TOPK_WAVES / WAVE], ps[2 * TOPK_MAX_CHUNKS * TOPK_WAVES / WAVE];
-  float gm = -INFINITY;
+    gm = wave_max(gm);
+    float gs = 0.f;
 #pragma unroll
-  for (int j = 0; j < 2 * TOPK_MAX_CHUNKS * TOPK_WAVES / WAVE; ++j) {
-    const int e = j * WAVE + lane;
-    pm[j] = -INFINITY;
-    ps[j] = 0.f;
-    if (e < G * TOPK_WAVES) {
-      const float2 p = cand_ms[(int64_t)row * G * TOPK_WAVES + e];
-      pm[j] = p.x;
-      ps[j] = p.y;
-    }
-    gm = fmaxf(gm, pm[j]);
+    for (int j = 0; j < PAIRS; ++j)
+      if (pm[j] != -INFINITY) gs += ps[j] * expf(pm[j] - gm);
+    gs = wave_sum(gs);
+    if (lane == 0) lse[row] = gm + logf(gs);
   }
-  gm = wave_max(gm);
-  float gs = 0.f;
+  __syncthreads();
+  if (tid >= WAVE) return;
+  // the next entry of each list is in a register before its head is popped
+  uint64_t head[2], next[2], mine = 0;
+  int at[2];
 #pragma unroll
-  for (int j = 0; j < 2 * TOPK_MAX_CHUNKS * TOPK_WAVES / WAVE; ++j)
-    if (pm[j] != -INFINITY) gs += ps[j] * expf(pm[j] - gm);
-  gs = wave_sum(gs);
-  if (lane == 0) lse[row] = gm + logf(gs);
-  wave_select(vals, ids, kk, top_val + row * KMAX, top_id + row * KMAX);
+  for (int j = 0; j < 2; ++j) {
+    const int c = j * WAVE + lane;
+    head[j] = c < nl ? list[c * KMAX] : 0;
+    next[j] = KMAX > 1 && c < nl ? list[c * KMAX + (KMAX > 1)] : 0;
+    at[j] = 2;
+  }
+  for (int q = 0; q < kk; ++q) {
+    const uint64_t top = wave_max_key(head[0] > head[1] ? head[0] : head[1]);
+    if (lane == q) mine = top;
+    if (top == 0) continue;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (head[j] == top) {
+        head[j] = next[j];
+        next[j] = at[j] < KMAX ? list[(j * WAVE + lane) * KMAX + at[j]] : 0;
+        ++at[j];
+      }
+  }
+  if (lane < kk) {
+    top_val[row * KMAX + lane] = key_value(mine);
+    top_id[row * KMAX + lane] = key_id(mine);
+  }
 }
 
 // Pool (see launch.h): device arrays of capacity C: token, score, depth, parent (pool index,
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(WAVE) void accept_greedy_kernel(const int32_t* __re
 
 // ----------------------------------------------------------------------------- host
 size_t row_topk_ws_bytes(int rows, int kmax) {
-  return (size_t)rows * TOPK_MAX_CHUNKS * (kmax * 8 + TOPK_WAVES * 8) + 256;
+  return (size_t)rows * TOPK_MAX_CHUNKS * ((kmax == 1 ? 1 : TOPK_WAVES * kmax) * 8 + TOPK_WAVES * 8) + 256;
 }
 
 adt_status launch_row_topk(const float* logits, int64_t ld, int V, const int32_t* allowed, int rows, int k, int kmax,
@@ -516,8 +519,7 @@ adt_status launch_row_topk(const float* logits, int64_t ld, int V, const int32_t
   ADT_CHECK_ARG(ws && ws_bytes >= row_topk_ws_bytes(rows, kmax), ADT_E_CAPACITY, "row_topk: workspace %zu < %zu", ws_bytes,
                 row_topk_ws_bytes(rows, kmax));
   float2* cms = (float2*)ws;
-  float* cv = (float*)(cms + (size_t)rows * G * TOPK_WAVES);
-  int* ci = (int*)(cv + (size_t)rows * G * kmax);
+  uint64_t* cand = (uint64_t*)(cms + (size_t)rows * G * TOPK_WAVES);
   // one range for every row: only the chunks it touches (the chunks past it held -inf only;
   // Anole's 8192 image codes of 65536 ids: 4 chunks instead of 32)
   int c0 = 0, Gr = G;
@@ -528,13 +530,13 @@ adt_status launch_row_topk(const float* logits, int64_t ld, int V, const int32_t
   }
   const dim3 g1(Gr, rows);
   if (kmax == 1) {
-    topk_chunk_kernel<1><<<g1, TOPK_THREADS, 0, st>>>(logits, ld, V, allowed, lo, hi, k, cv, ci, cms, c0);
+    topk_chunk_kernel<1><<<g1, TOPK_THREADS, 0, st>>>(logits, ld, V, allowed, lo, hi, k, cand, cms, c0);
     ADT_LAUNCH_CHECK();
-    topk_merge_kernel<1><<<rows, WAVE, 0, st>>>(cv, ci, cms, Gr, V, allowed, lo, hi, k, top_id, top_val, lse);
+    topk_merge_kernel<1><<<rows, TOPK_THREADS, 0, st>>>(cand, cms, Gr, V, allowed, lo, hi, k, top_id, top_val, lse);
   } else {
-    topk_chunk_kernel<16><<<g1, TOPK_THREADS, 0, st>>>(logits, ld, V, allowed, lo, hi, k, cv, ci, cms, c0);
+    topk_chunk_kernel<16><<<g1, TOPK_THREADS, 0, st>>>(logits, ld, V, allowed, lo, hi, k, cand, cms, c0);
     ADT_LAUNCH_CHECK();
-    topk_merge_kernel<16><<<rows, WAVE, 0, st>>>(cv, ci, cms, Gr, V, allowed, lo, hi, k, top_id, top_val, lse);
+    topk_merge_kernel<16><<<rows, TOPK_THREADS, 0, st>>>(cand, cms, Gr, V, allowed, lo, hi, k, top_id, top_val, lse);
   }
   ADT_LAUNCH_CHECK();
   return ADT_OK;

@@ -212,6 +212,27 @@ def test_expand_from_table_bit_exact(rt, d_hat, k_hat, n_budget):
     assert np.array_equal(t["mask"].cpu().numpy().view(np.uint64), packed_mask(ref.parent, 2))
 
 
+@pytest.mark.parametrize("vocab,lo,hi,k", [(1500, 0, 1500, 13), (2049, 2040, 2049, 13), (16384, 3000, 9000, 10),
+                                           (65536, 0, 65536, 13), (65536, 65530, 65536, 1)])
+def test_expand_root_top_k_with_ties(rt, vocab, lo, hi, k):
+    """The root's top-k over one to 32 chunks, ranges that begin and end inside a chunk and hold
+    fewer ids than k, and logits on a 0.5 grid (hundreds of equal ones at the boundary): ids in
+    (logit descending, id ascending) order, scores to fp32 rounding."""
+    cfg = synth.shrink(synth.get_config("tiny"), vocab=vocab)
+    cfg = dataclasses.replace(cfg, img_lo=lo, img_hi=hi, sched=dataclasses.replace(cfg.sched, d_hi=1, k_hi=13, n_budget=60))
+    _, om, dm, pre = _setup(rt, cfg)
+    table = np.round(synth.draw_tensor(78, 5, (3, vocab), False, std=np.float32(2.0)) * 2) / 2
+    sess = rt.DeviceSession(dm, cfg, draft_table=torch.from_numpy(table).cuda())
+    root = sess.prefill(pre)
+    n = sess.expand(1, k, 60)
+    row = table[_table_row(0, root, 3)].astype(np.float64)[lo:hi]
+    ids = np.lexsort((np.arange(lo, hi), -row))[:k]
+    t = sess.tensors()
+    assert n == len(ids) + 1 and t["token"].cpu().tolist()[1:n] == (ids + lo).tolist()
+    lse = np.log(np.exp(row - row.max()).sum()) + row.max()
+    np.testing.assert_allclose(t["score"].cpu().numpy()[1:n], row[ids] - lse, atol=2e-5, rtol=1e-6)
+
+
 @pytest.mark.parametrize("d_hat,k_hat,children,n_budget,top_k,T", [(1, 4, 3, 16, 0, 1.0), (3, 4, 3, 16, 0, 1.0),
                                                                     (6, 10, 4, 60, 50, 0.8), (9, 13, 2, 127, 0, 1.3),
                                                                     (4, 2, 16, 60, 0, 1.0)])

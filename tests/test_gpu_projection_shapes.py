@@ -24,7 +24,7 @@ def rt():
     return runtime
 
 
-def _check_verify(rt, cfg, n, seed=0, by_row=False):
+def _check_verify(rt, cfg, n, seed=0, by_row=False, passes=1):
     """by_row (wide bf16 models): one unmirrored bf16 rounding is amplified by sums over
     thousands of columns past the element tolerance, whatever computes it, so each logit row is
     compared by its 2-norm.  The two sides round at the same eight storage points of a layer
@@ -46,7 +46,9 @@ def _check_verify(rt, cfg, n, seed=0, by_row=False):
     token = rng.integers(cfg.img_lo, cfg.img_hi, size=n).astype(np.int32)
     token[0] = root
     sess.set_tree(parent, token)
-    sess.verify()
+    for _ in range(passes):
+        sess.tensors()["logits"].zero_()
+        sess.verify()
     got = sess.tensors()["logits"].cpu().numpy()
     L, d = dec.L, depths(parent)
     keys = [list(range(L)) + [L + j for j in a] for a in ancestors_and_self(parent)]
@@ -91,3 +93,14 @@ def test_verify_bf16_row_groups(rt, heads, ffn, n):
     cfg = synth.shrink(synth.get_config("llamagen_xl"), n_layers=2, d_model=d, n_heads=heads, ffn=ffn, vocab=2064)
     cfg = dataclasses.replace(cfg, prefix_len=70, img_hi=2064, prefix_hi=2064, grid_h=8, grid_w=16)
     _check_verify(rt, cfg, n, by_row=d > 1024)
+
+
+@pytest.mark.parametrize("head_dim,n", [(64, 1), (64, 16), (64, 33), (64, 127), (128, 1), (128, 16), (128, 40), (128, 127)])
+def test_verify_bf16_key_splits(rt, head_dim, n):
+    """Attention over a 128-token prefix and its tree, whose key blocks stay in one split or are
+    merged by the last of two splits to arrive; the forward is replayed, so the arrival counters of one
+    pass serve the next."""
+    cfg = synth.shrink(synth.get_config("llamagen_xl"), n_layers=2, d_model=4 * head_dim, n_heads=4, head_dim=head_dim,
+                       ffn=256, vocab=1024)
+    cfg = dataclasses.replace(cfg, prefix_len=128, img_hi=1024, prefix_hi=1024, grid_h=32, grid_w=32)
+    _check_verify(rt, cfg, n, passes=3)
