@@ -1023,8 +1023,10 @@ static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t*
     TRY(gemm_p(s->att, dm, m->o[l], rows, dm, dm, dt, s->part, st));
     TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, s->act, dt, st));
     TRY(capt_snap(s, 2 * (l - l0) + 1, st));
-    TRY(gemm_p(s->act, dm, m->gu[l], rows, 2 * F, dm, dt, s->part, st));
-    TRY(launch_swiglu(s->part, 1, rows, F, s->sw, dt, st));
+    GemmEpi sw;
+    sw.mode = EPI_SWIGLU;
+    sw.out = (float*)s->sw;
+    TRY(gemm_p(s->act, dm, m->gu[l], rows, 2 * F, dm, dt, s->part, st, sw));
     TRY(gemm_p(s->sw, F, m->down[l], rows, dm, F, dt, s->part, st));
     TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, l + 1 == l1 ? final_out : s->act, dt, st));
   }
@@ -1047,8 +1049,7 @@ static adt_status lm_head(adt_session_s* s, const void* feat_rows, int ldx, int 
     const void* w = (const uint16_t*)s->m->d.lm_head + (size_t)s->lm_lo * s->dm;
     TRY(gemm_p(feat_rows, ldx, w, rows, s->lm_hi - s->lm_lo, s->dm, s->dt, s->part, st, e));
   } else {
-    TRY(gemm_p(feat_rows, s->dm, s->m->d.lm_head, rows, s->V, s->dm, s->dt, s->part, st));
-    TRY(launch_reduce_store(s->part, 1, rows, s->V, dst, s->V, st));
+    TRY(gemm_p(feat_rows, s->dm, s->m->d.lm_head, rows, s->V, s->dm, s->dt, dst, st));   // dst is [rows][V]
   }
   if (s->nb > 1) TRY(launch_guide_rows(raw, M, s->V, s->gscale, out, s->V, st));
   return ADT_OK;

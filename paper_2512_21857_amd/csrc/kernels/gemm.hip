@@ -546,12 +546,13 @@ __global__ __launch_bounds__(TILE_THREADS, 2) void gemm_rows_dma_kernel(const ui
 // sums stay as short as a lane-strided sum's); accumulators, then waves, are added pairwise.  One wave per column with the rows read one by one had taken 24-72 us a
 // launch at 17 rows (K 256 and 1024): 377 -> 104 us for the two-layer model's 17-row forward.
 // W and X rows need 4-byte alignment only; K is a multiple of 16; rows past M or N repeat the last.
+// With act the gate/up product stores silu(gate) up there instead (a launch of its own took 2.5 us).
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int MR, int U>
 __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ X, int ldx,
                                                                 const float* __restrict__ W, int M, int N, int K,
-                                                                float* __restrict__ part) {
+                                                                float* __restrict__ part, float* __restrict__ act) {
   __shared__ f32x4 red[TILE_WAVES][MR][WAVE];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int lane = threadIdx.x % WAVE, lq = lane & 15, g = lane >> 4;
@@ -611,7 +612,13 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __r
         for (int r = 0; r < 4; ++r) v[w][r] += v[w + h][r];
     const f32x4 y = v[0];
     const int row = m0 + wave * 16 + lq, n = n0 + 4 * g;
-    if (row < M) {
+    if (act) {   // gate columns in lanes g < 2, the up columns that match them in lanes g + 2
+      const f32x4 u = shfl_xor4(y, 32);
+      if (row < M && g < 2 && n < N)
+        *reinterpret_cast<f32x4_a4*>(act + (int64_t)row * (N / 2) + n0 / 2 + 4 * g) =
+            f32x4{y[0] / (1.f + expf(-y[0])) * u[0], y[1] / (1.f + expf(-y[1])) * u[1],
+                  y[2] / (1.f + expf(-y[2])) * u[2], y[3] / (1.f + expf(-y[3])) * u[3]};
+    } else if (row < M) {
       float* dst = part + (int64_t)row * N + n;
       if (n + 4 <= N) {
         *reinterpret_cast<f32x4_a4*>(dst) = y;
@@ -792,9 +799,11 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
     // (17 rows: 32-256 workgroups), else up to four, so that a tile's weights are read fewer times
     const int tiles = (N + 15) / 16, mb = (M + 15) / 16;
     const float *x = (const float*)X, *w = (const float*)Wp;
+    float* act = epi.mode == EPI_SWIGLU ? epi.out : nullptr;
+    ADT_CHECK_ARG(epi.mode != EPI_SWIGLU || (act && N % 16 == 0), ADT_E_ARG, "gemm f32: SwiGLU output of N=%d", N);
 #define ADT_GF(MRV, UV)                                                                                               \
   hipExtLaunchKernelGGL((gemm_f32_kernel<MRV, UV>), dim3(tiles, (mb + MRV - 1) / MRV), dim3(TILE_THREADS), 0, st, ev0, \
-                        ev1, 0, x, ldx, w, M, N, K, part)
+                        ev1, 0, x, ldx, w, M, N, K, part, act)
     if ((int64_t)tiles * mb <= 512) ADT_GF(1, 8);
     else if ((int64_t)tiles * mb <= 1024) ADT_GF(2, 4);
     else ADT_GF(4, 4);

@@ -393,17 +393,6 @@ __global__ __launch_bounds__(ROW_THREADS) void swiglu_kernel(const float* __rest
   Elem<T>::store(o, 3, g.w / (1.f + expf(-g.w)) * u.w);
 }
 
-// out[m][n] = sum_s part[s][m][n]  (logits).
-__global__ void reduce_store_kernel(const float* __restrict__ part, int splits, int M, int N, float* __restrict__ out,
-                                    int64_t ldo) {
-  const int m = blockIdx.y;
-  for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < N; n += gridDim.x * blockDim.x) {
-    float y = 0.f;
-    for (int s = 0; s < splits; ++s) y += part[((int64_t)s * M + m) * N + n];
-    out[(int64_t)m * ldo + n] = y;
-  }
-}
-
 // dst[i] = src[idx[i]] for i < cnt (rows of length d, element type T).
 template <typename T>
 __global__ void gather_rows_kernel(const T* __restrict__ src, const int32_t* __restrict__ idx, int d,
@@ -667,13 +656,6 @@ adt_status launch_swiglu(const float* part, int splits, int M, int F, void* out,
   ADT_CHECK_ARG(F % 16 == 0, ADT_E_SHAPE, "swiglu: F=%d", F);
   dim3 grid(M, (F / 4 + ROW_THREADS - 1) / ROW_THREADS);
   ADT_DISPATCH_T(dtype, swiglu_kernel<T><<<grid, ROW_THREADS, 0, st>>>(part, splits, M, F, (T*)out));
-  ADT_LAUNCH_CHECK();
-  return ADT_OK;
-}
-
-adt_status launch_reduce_store(const float* part, int splits, int M, int N, float* out, int64_t ldo, hipStream_t st) {
-  dim3 grid((N + 1023) / 1024 < 64 ? (N + 1023) / 1024 : 64, M);
-  reduce_store_kernel<<<grid, 1024, 0, st>>>(part, splits, M, N, out, ldo);
   ADT_LAUNCH_CHECK();
   return ADT_OK;
 }

@@ -88,7 +88,7 @@ struct GemmEpi {
   int slot_cap = 0;        // cache slots per head (> 0: rows whose slot would pass it are not
                            // stored; debug builds record them)
   // EPI_SWIGLU (weights packed with ADT_PACK_GATE_UP): act[m][N/2] = silu(gate) * up, in
-  // the fragment layout of act_pk row blocks (0: row-major)
+  // the fragment layout of act_pk row blocks (0: row-major); an fp32 product stores it in out, row-major
   uint16_t* act = nullptr;
   int act_pk = 0;
   // EPI_RESID (one K range): resid[m][n] (fp32, [M][N]) += Y (assign: = Y), then act[m][n] =
@@ -159,7 +159,6 @@ adt_status launch_qkv_rows(const float* C, int M, int H, int Dh, const int32_t* 
                            const int32_t* seq, const float2* rope, void* qout, void* kc, void* vc, int64_t stride_h,
                            int64_t cache_sb, int dtype, hipStream_t st);
 adt_status launch_swiglu(const float* part, int splits, int M, int F, void* out, int dtype, hipStream_t st);
-adt_status launch_reduce_store(const float* part, int splits, int M, int N, float* out, int64_t ldo, hipStream_t st);
 adt_status launch_gather_rows(const void* src, const int32_t* idx, int cnt, int d, void* dst, int dtype,
                               hipStream_t st);
 adt_status launch_kv_compact(void* k, void* v, int B, int slices, int Dh, int64_t sb, int64_t ss, const int32_t* kv_len,
