@@ -786,14 +786,9 @@ static SmallI32 small_of(const int32_t* v, int n) {
   return s;
 }
 
-// Device scalars of a forward, one copy per guidance branch: scal[0..1] attention prefix
-// length, [2..3] query rows, [4..5] tail rows; scal[6] first cache slot of the rows;
-// scal[8..9] the committed length for compaction.
+// Device scalars: scal[0..6] those of the forward (FwdScalars), scal[8..9] the committed length
+// for compaction.
 enum { SC_KV = 0, SC_NQ = 2, SC_TAIL = 4, SC_SLOT = 6, SC_CL = 8 };
-static adt_status set_scalars(adt_session_s* s, int kv_len, int nq, int ntail, int slot0, hipStream_t st) {
-  int32_t v[7] = {kv_len, kv_len, nq, nq, ntail, ntail, slot0};
-  return launch_set_i32(s->scal, small_of(v, 7), 7, st);
-}
 
 // Runs body(stream) through a cached graph (captured on first use for this key).  Eager
 // when graphs are off or the profiling hook is on (events cannot be recorded per kernel
@@ -1061,13 +1056,14 @@ static adt_status lm_head(adt_session_s* s, const void* feat_rows, int ldx, int 
 static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, const int32_t* pos, int slot0, int L_pre,
                                  int n_tail, const uint64_t* mask, int lm_row0, int lm_rows, hipStream_t st,
                                  int64_t key = -1, int tok_boff = 0) {
-  TRY(set_scalars(s, L_pre, M, n_tail, slot0, st));
+  const int pk = act_blocks(s, s->nb * M);
+  // The embedding rows and, in the same launch, the scalars that change from call to call (outside
+  // the graph for their sake; a launch of their own took 2-4.6 us).  bf16: act takes the raw
+  // embedding rows (the first projection normalises them).
+  TRY(launch_embed_norm(s->m->d.embed, tok, s->nb * M, s->dm, s->m->d.norm_eps, s->h, s->act, s->dt, st,
+                        Branches{s->nb, tok_boff, 0}, pk, pk > 0, FwdScalars{s->scal, L_pre, M, n_tail, slot0}));
   auto body = [&](hipStream_t cs) -> adt_status {
     TRY(capt_begin(s, false, M, L_pre, slot0, n_tail, tok, pos, mask, cs));
-    const int pk = act_blocks(s, s->nb * M);
-    // bf16: act takes the raw embedding rows (the first projection normalises them)
-    TRY(launch_embed_norm(s->m->d.embed, tok, s->nb * M, s->dm, s->m->d.norm_eps, s->h, s->act, s->dt, cs,
-                          Branches{s->nb, tok_boff, 0}, pk, pk > 0));
     // logits of every row read the final norm from act in the fragment layout
     const bool all = pk && lm_row0 == 0 && lm_rows == M;
     TRY(run_layers(s, false, M, pos, slot0, L_pre, n_tail, mask, s->feat, all, cs));
@@ -1088,14 +1084,13 @@ static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, co
 static adt_status draft_forward(adt_session_s* s, const int32_t* tok, const int32_t* fsrc, const void* fa, int M,
                                 const int32_t* pos, int slot0, int L_pre, int n_tail, const uint64_t* mask, void* fout,
                                 int lm_row0, int lm_rows, float* lout, float* lraw, hipStream_t st, int64_t key = -1,
-                                int tok_boff = 0) {
+                                int tok_boff = 0, const CatchUp& cu = {}) {
   const int dm = s->dm, dt = s->dt, rows = s->nb * M;
-  TRY(set_scalars(s, L_pre, M, n_tail, slot0, st));
+  const int pk = act_blocks(s, rows);
+  TRY(launch_draft_input(s->m->d.embed, tok, fsrc, fa, s->dfeat, rows, dm, s->xin, dt, st,
+                         Branches{s->nb, tok_boff, 0}, pk, FwdScalars{s->scal, L_pre, M, n_tail, slot0}, cu));
   auto body = [&](hipStream_t cs) -> adt_status {
     TRY(capt_begin(s, true, M, L_pre, slot0, n_tail, tok, pos, mask, cs));
-    const int pk = act_blocks(s, rows);
-    TRY(launch_draft_input(s->m->d.embed, tok, fsrc, fa, s->dfeat, rows, dm, s->xin, dt, cs,
-                           Branches{s->nb, tok_boff, 0}, pk));
     if (s->capt_cur >= 0)   // the captured FC input is row-major
       TRY(launch_draft_input(s->m->d.embed, tok, fsrc, fa, s->dfeat, rows, dm,
                              (char*)s->capt.xin + s->capt_log[s->capt_cur].xin_off, dt, cs,
@@ -1303,9 +1298,9 @@ extern "C" adt_status adt_tree_expand(adt_session* s, int32_t d_hat, int32_t k_h
     TRY(launch_table_rows(s->ctok + (cu - 1), 1, 0, trows, s->idx, st));
     TRY(launch_gather_rows(s->d.draft_table, s->idx, 1, V, s->dlogits, ADT_F32, st));
   } else {
-    TRY(launch_catchup_rows(small_of(ctok.data(), cu), cu, Ld, s->ctok, s->cfsrc, s->cpos, s->cmask, st));
+    const CatchUp rows{cu, Ld, s->ctok, s->cfsrc, s->cpos, s->cmask, small_of(ctok.data(), cu)};
     TRY(draft_forward(s, s->ctok, s->cfsrc, s->cfeat, cu, s->cpos, Ld, Ld, cu, s->cmask, s->dfeat, cu - 1, 1,
-                      s->dlogits, s->draw, st, gkey(2, 0, 0, cu)));
+                      s->dlogits, s->draw, st, gkey(2, 0, 0, cu), 0, rows));
   }
   int lo, hi;
   cell_range(s, L + 1 - P, lo, hi);

@@ -18,9 +18,11 @@ ADT_DEVICE_ERROR_WORD(rows)
 template <typename T>
 __global__ __launch_bounds__(ROW_THREADS) void embed_norm_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok,
                                                                  int d, float eps, float* __restrict__ h,
-                                                                 T* __restrict__ a, Branches br, int a_pk, int raw) {
+                                                                 T* __restrict__ a, Branches br, int a_pk, int raw,
+                                                                 FwdScalars fs) {
   __shared__ float red[16];
   const int m = blockIdx.x;
+  if (m == 0) set_fwd_scalars(fs, threadIdx.x);
   const T* e = E + (int64_t)tok[m / br.nb + (m % br.nb) * br.tok_boff] * d;
   float ss = 0.f;
   for (int i = threadIdx.x; i < d; i += blockDim.x) {
@@ -39,9 +41,10 @@ template <int VPT>
 __global__ __launch_bounds__(ROW_THREADS) void embed_norm_bf16_kernel(const uint16_t* __restrict__ E,
                                                                       const int32_t* __restrict__ tok, int d, float eps,
                                                                       float* __restrict__ h, uint16_t* __restrict__ a,
-                                                                      Branches br, int a_pk, int raw) {
+                                                                      Branches br, int a_pk, int raw, FwdScalars fs) {
   __shared__ float red[16];
   const int m = blockIdx.x;
+  if (m == 0) set_fwd_scalars(fs, threadIdx.x);
   const uint16_t* e = E + (int64_t)tok[m / br.nb + (m % br.nb) * br.tok_boff] * d;
   u16x8 v[VPT];
 #pragma unroll
@@ -129,10 +132,15 @@ __global__ __launch_bounds__(ROW_THREADS) void draft_input_bf16_kernel(const uin
                                                                        const int32_t* __restrict__ fsrc,
                                                                        const uint16_t* __restrict__ fa,
                                                                        const uint16_t* __restrict__ fb, int d,
-                                                                       uint16_t* __restrict__ x, Branches br, int x_pk) {
+                                                                       uint16_t* __restrict__ x, Branches br, int x_pk,
+                                                                       FwdScalars fs, CatchUp cu) {
   const int m = blockIdx.x, node = m / br.nb, b = m % br.nb;
-  const uint16_t* e = E + (int64_t)tok[node + b * br.tok_boff] * d;
-  const int s = fsrc[node];
+  if (m == 0) {
+    set_fwd_scalars(fs, threadIdx.x);
+    set_catch_up(cu, threadIdx.x);
+  }
+  const uint16_t* e = E + (int64_t)(cu.cu ? cu.tok.v[node] : tok[node + b * br.tok_boff]) * d;
+  const int s = cu.cu ? node : fsrc[node];
   const uint16_t* f = s >= 0 ? fa + ((int64_t)s * br.nb + b) * d
                              : (s <= -2 ? fb + ((int64_t)(-s - 2) * br.nb + b) * d : nullptr);
   u16x8 ev[VPT], fv[VPT];
@@ -203,10 +211,15 @@ template <typename T>
 __global__ __launch_bounds__(ROW_THREADS) void draft_input_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok,
                                                                   const int32_t* __restrict__ fsrc, const T* __restrict__ fa,
                                                                   const T* __restrict__ fb, int d, T* __restrict__ x,
-                                                                  Branches br, int x_pk) {
+                                                                  Branches br, int x_pk, FwdScalars fs,
+                                                                  CatchUp cu) {
   const int m = blockIdx.x, node = m / br.nb, b = m % br.nb;
-  const T* e = E + (int64_t)tok[node + b * br.tok_boff] * d;
-  const int s = fsrc[node];
+  if (m == 0) {
+    set_fwd_scalars(fs, threadIdx.x);
+    set_catch_up(cu, threadIdx.x);
+  }
+  const T* e = E + (int64_t)(cu.cu ? cu.tok.v[node] : tok[node + b * br.tok_boff]) * d;
+  const int s = cu.cu ? node : fsrc[node];
   // feature sources hold the branches of one node in consecutive rows
   const T* f = s >= 0 ? fa + ((int64_t)s * br.nb + b) * d
                       : (s <= -2 ? fb + ((int64_t)(-s - 2) * br.nb + b) * d : nullptr);
@@ -518,7 +531,7 @@ static bool frag_ok(int pk, int M, int K, int dtype) {
 }
 
 adt_status launch_embed_norm(const void* E, const int32_t* tok, int M, int d, float eps, float* h, void* a, int dtype,
-                             hipStream_t st, const Branches& br, int a_pk, bool raw) {
+                             hipStream_t st, const Branches& br, int a_pk, bool raw, const FwdScalars& fs) {
   ADT_CHECK_ARG(a != nullptr && h != nullptr, ADT_E_ARG, "embed_norm: outputs");
   ADT_CHECK_ARG(frag_ok(a_pk, M, d, dtype), ADT_E_SHAPE, "embed_norm: fragment layout of %d blocks for %d x %d", a_pk,
                 M, d);
@@ -526,14 +539,14 @@ adt_status launch_embed_norm(const void* E, const int32_t* tok, int M, int d, fl
     const int vpt = (d + 8 * ROW_THREADS - 1) / (8 * ROW_THREADS);
 #define ADT_EN(V)                                                                                                 \
   embed_norm_bf16_kernel<V><<<M, ROW_THREADS, 0, st>>>((const uint16_t*)E, tok, d, eps, h, (uint16_t*)a, br, a_pk, \
-                                                       raw ? 1 : 0)
+                                                       raw ? 1 : 0, fs)
     if (vpt <= 1) ADT_EN(1);
     else if (vpt <= 2) ADT_EN(2);
     else ADT_EN(4);
 #undef ADT_EN
   } else {
     ADT_DISPATCH_T(dtype, embed_norm_kernel<T><<<M, ROW_THREADS, 0, st>>>((const T*)E, tok, d, eps, h, (T*)a, br, a_pk,
-                                                                           raw ? 1 : 0));
+                                                                           raw ? 1 : 0, fs));
   }
   ADT_LAUNCH_CHECK();
   return ADT_OK;
@@ -593,21 +606,23 @@ adt_status launch_resid_add(const float* part, int S, int M, int d, int assign, 
 }
 
 adt_status launch_draft_input(const void* E, const int32_t* tok, const int32_t* fsrc, const void* fa, const void* fb,
-                              int M, int d, void* x, int dtype, hipStream_t st, const Branches& br, int x_pk) {
+                              int M, int d, void* x, int dtype, hipStream_t st, const Branches& br, int x_pk, const FwdScalars& fs, const CatchUp& cu) {
+  ADT_CHECK_ARG(cu.cu == 0 || (cu.cu >= 1 && cu.cu <= 32 && M == cu.cu * br.nb && br.tok_boff == 0), ADT_E_ARG,
+                "draft_input: %d catch-up rows", cu.cu);
   ADT_CHECK_ARG(frag_ok(x_pk, M, 2 * d, dtype), ADT_E_SHAPE, "draft_input: fragment layout of %d blocks for %d x %d",
                 x_pk, M, 2 * d);
   if (dtype == ADT_BF16 && d % 8 == 0 && d <= 4 * 8 * ROW_THREADS) {
     const int vpt = (d + 8 * ROW_THREADS - 1) / (8 * ROW_THREADS);
 #define ADT_DI(V)                                                                                                  \
   draft_input_bf16_kernel<V><<<M, ROW_THREADS, 0, st>>>((const uint16_t*)E, tok, fsrc, (const uint16_t*)fa,       \
-                                                        (const uint16_t*)fb, d, (uint16_t*)x, br, x_pk)
+                                                        (const uint16_t*)fb, d, (uint16_t*)x, br, x_pk, fs, cu)
     if (vpt <= 1) ADT_DI(1);
     else if (vpt <= 2) ADT_DI(2);
     else ADT_DI(4);
 #undef ADT_DI
   } else {
     ADT_DISPATCH_T(dtype, draft_input_kernel<T><<<M, ROW_THREADS, 0, st>>>((const T*)E, tok, fsrc, (const T*)fa,
-                                                                            (const T*)fb, d, (T*)x, br, x_pk));
+                                                                            (const T*)fb, d, (T*)x, br, x_pk, fs, cu));
   }
   ADT_LAUNCH_CHECK();
   return ADT_OK;

@@ -15,6 +15,38 @@ struct Branches {
   int64_t cache_sb = 0;
 };
 
+// Device scalars of a forward, written by its first kernel (dst null: none): dst[0..1] attention
+// prefix length, one copy per guidance branch, [2..3] query rows, [4..5] tail rows; dst[6] first
+// cache slot of the rows.
+struct FwdScalars {
+  int32_t* dst = nullptr;
+  int32_t kv_len = 0, nq = 0, n_tail = 0, slot0 = 0;
+};
+// (thread i < 7 of one workgroup)
+__device__ __forceinline__ void set_fwd_scalars(const FwdScalars& f, int i) {
+  if (f.dst && i < 7) f.dst[i] = i < 2 ? f.kv_len : (i < 4 ? f.nq : (i < 6 ? f.n_tail : f.slot0));
+}
+
+struct SmallI32 {
+  int32_t v[32];
+};
+// The draft's catch-up rows, laid out by the draft input's launch (cu = 0: none; cu <= 32 nodes):
+// tokens from the arguments, feature sources 0..cu-1, positions pos0.., the masks of a chain.
+struct CatchUp {
+  int32_t cu = 0, pos0 = 0;
+  int32_t *tok_out = nullptr, *fsrc = nullptr, *pos = nullptr;
+  uint64_t* mask = nullptr;
+  SmallI32 tok{};
+};
+__device__ __forceinline__ void set_catch_up(const CatchUp& c, int i) {
+  if (i >= c.cu) return;
+  c.tok_out[i] = c.tok.v[i];
+  c.fsrc[i] = i;
+  c.pos[i] = c.pos0 + i;
+  c.mask[i * 2] = (1ull << (i + 1)) - 1;
+  c.mask[i * 2 + 1] = 0;
+}
+
 // Device error words of the source files whose kernels test invariants (debug builds; 0 in
 // release builds): read and cleared, with the current device synchronised by the copy.
 uint32_t dev_errors_take_rows();
@@ -129,7 +161,7 @@ size_t gemm_nt_part_elems(int M, int N, int K);
 // h = embedding rows, a = RMSNorm(h) (raw: h itself) in the model dtype (bf16: fragment
 // layout of a_pk row blocks when a_pk > 0, else row-major).
 adt_status launch_embed_norm(const void* E, const int32_t* tok, int M, int d, float eps, float* h, void* a, int dtype,
-                             hipStream_t st, const Branches& br = Branches{}, int a_pk = 0, bool raw = false);
+                             hipStream_t st, const Branches& br = Branches{}, int a_pk = 0, bool raw = false, const FwdScalars& fs = {});
 // The residual projection's finish, one row per workgroup: y = sum over s < S of part[s][m][:]
 // (in s order), h[m] = y (assign) or h[m] + y, then RMSNorm(h[m]) in the model dtype into out
 // (layout out_pk: the next projection's input, or the final features) and, if out2 is given,
@@ -146,7 +178,7 @@ adt_status launch_resid_add(const float* part, int S, int M, int d, int assign, 
 // row-major, or in the fragment layout of x_pk row blocks.
 adt_status launch_draft_input(const void* E, const int32_t* tok, const int32_t* fsrc, const void* fa, const void* fb,
                               int M, int d, void* x, int dtype, hipStream_t st, const Branches& br = Branches{},
-                              int x_pk = 0);
+                              int x_pk = 0, const FwdScalars& fs = {}, const CatchUp& cu = {});
 adt_status launch_add_norm(const float* part, int splits, int M, int d, int assign, float eps, float* h, void* a,
                            int dtype, hipStream_t st);
 adt_status launch_rope_table(float2* tab, int positions, int Dh, double theta, hipStream_t st);
@@ -209,14 +241,8 @@ adt_status launch_accept_greedy(const int32_t* argmax, int kmax, const int32_t* 
                                 hipStream_t st);
 
 // small.hip
-struct SmallI32 {
-  int32_t v[32];
-};
 adt_status launch_set_i32(int32_t* dst, const SmallI32& vals, int count, hipStream_t st);
 adt_status launch_fill_pairs(int32_t* dst, int rows, int lo, int hi, hipStream_t st);
-// The draft catch-up rows (cu <= 32): ctok = tok, cfsrc = 0..cu-1, cpos = Ld.., chain masks.
-adt_status launch_catchup_rows(const SmallI32& tok, int cu, int Ld, int32_t* ctok, int32_t* cfsrc, int32_t* cpos,
-                               uint64_t* cmask, hipStream_t st);
 adt_status launch_table_rows(const int32_t* tok, int count, int depth, int rows, int32_t* idx, hipStream_t st);
 adt_status launch_iota(int32_t* dst, int count, int start, int step, hipStream_t st);
 adt_status launch_chain_masks(uint64_t* mask, int n, hipStream_t st);
