@@ -528,7 +528,7 @@ __device__ int balanced_seq(int y, int B, const int32_t* kv_len, const int32_t* 
   return b;
 }
 
-template <int DH, int KH, int NW, int P>
+template <int DH, int KH, int NW, int P, bool MERGE = false>
 __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
     int64_t stride_b, int64_t stride_h, const int32_t* __restrict__ kv_len, const int32_t* __restrict__ n_q,
@@ -561,11 +561,11 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
   // with splits > 1, split sp takes a contiguous share of the live blocks (balanced on the
   // device, so a replayed launch follows the growing prefix)
   const int nblk_all = (total + BLK_KT - 1) / BLK_KT;
-  const int even = (nblk_all + splits - 1) / splits, per = arrived ? max(even, ATT_MIN_BLOCKS) : even;
+  const int even = (nblk_all + splits - 1) / splits, per = MERGE ? max(even, ATT_MIN_BLOCKS) : even;
   const int blk0 = min(nblk_all, sp * per), nblk = min(nblk_all, blk0 + per);
-  // splits with keys; without `arrived` the empty ones store empty partials for the merge launch
-  const int live = arrived ? max(1, (nblk_all + per - 1) / per) : splits;
-  if (sp >= live) return;
+  // splits with keys; without MERGE the empty ones store empty partials for the merge launch
+  const int live = MERGE ? max(1, (nblk_all + per - 1) / per) : splits;
+  if (MERGE && sp >= live) return;
   const uint16_t* kbase = kc + b * stride_b + h * stride_h;
   const uint16_t* vbase = vc + b * stride_b + h * stride_h;
 
@@ -758,7 +758,7 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
       for (int d = 0; d < DT; ++d)
         store4(out + rl.o_index(b, qr, H, DH, h, d * 16 + 4 * g), o[d][0] * inv, o[d][1] * inv, o[d][2] * inv,
                o[d][3] * inv);
-    } else if (P > 1 && arrived) {
+    } else if (MERGE) {
       const int64_t pr = (((int64_t)b * H + h) * splits + sp) * nq_max + qr;
 #pragma unroll
       for (int d = 0; d < DT; ++d) {
@@ -777,11 +777,13 @@ __global__ __launch_bounds__(NW * WAVE, P > 1 ? 2 : 4) void tree_attn_blk_kernel
       }
     }
   }
-  // The last split of the pair to get here merges them all, in split order, four dims of one
+  // MERGE (a session's forwards, whose counters are zero between launches; a template parameter, as
+  // the code alone cost the other launches 0.1 us of 18.7):
+  // the last split of the pair to get here merges them all, in split order, four dims of one
   // query a thread: the partials of a split are complete at the agent's coherence point (write-
   // through stores, waited for) before its arrival counts, and are read past the local caches.
-  if constexpr (P > 1) {
-    if (!arrived || live == 1) return;
+  if constexpr (MERGE) {
+    if (live == 1) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();   // (and the merge area of the key parts has been read)
     uint32_t* last = reinterpret_cast<uint32_t*>(smem);
@@ -899,14 +901,16 @@ static adt_status attn_bf16(const void* q, const void* k, const void* v, int64_t
   const int qt = (nq_max + 15) / 16;
   const bool merge = S > 1 && !arrived;   // partials merged by a launch of its own
   hipEvent_t e1 = merge ? nullptr : ev1;
-#define ADT_ATTN_BLK_P(DHV, KHV, NWV, PV)                                                                       \
-  hipExtLaunchKernelGGL(tree_attn_blk_kernel<DHV, KHV, NWV, PV>, grid, dim3(NWV * WAVE), 0, st, ev0, e1, 0,        \
+#define ADT_ATTN_BLK_P(DHV, KHV, NWV, ...)                                                                      \
+  hipExtLaunchKernelGGL((tree_attn_blk_kernel<DHV, KHV, NWV, __VA_ARGS__>), grid, dim3(NWV * WAVE), 0, st, ev0, e1, 0, \
                         (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, sb, sh, kv_len, n_q, n_tail,   \
-                        mask, rl, H, nq_max, kv_cap, sl2, (uint16_t*)out, S, part_o, part_ml, S > 1 ? arrived : nullptr)
+                        mask, rl, H, nq_max, kv_cap, sl2, (uint16_t*)out, S, part_o, part_ml, arrived)
   // a split workgroup owns the CU and streams a few blocks, so it keeps three in flight; many
   // pairs without splits keep one (two workgroups share a CU)
 #define ADT_ATTN_BLK(DHV, KHV, NWV)        \
-  if (S > 1) {                             \
+  if (S > 1 && arrived) {                  \
+    ADT_ATTN_BLK_P(DHV, KHV, NWV, 3, true); \
+  } else if (S > 1) {                      \
     ADT_ATTN_BLK_P(DHV, KHV, NWV, 3);      \
   } else {                                 \
     ADT_ATTN_BLK_P(DHV, KHV, NWV, 1);      \
