@@ -143,21 +143,23 @@ __global__ __launch_bounds__(NT_THREADS) void gemm_nt_kernel(const uint16_t* __r
 // Pipeline, per stage kt: the fragments of the stage's second half are read while the first
 // half's eight MFMAs run; each wave waits for its own DMA of stage kt+1 (the NSTAGE-3 newer
 // stages stay in flight) and one barrier publishes it; the DMA of stage kt+NSTAGE-1 then
-// refills the slot of stage kt-1, whose fragments every wave consumed before that barrier;
-// the next stage's first fragments are read while the second half's MFMAs run.  The DMA and
+// refills the slot of stage kt-1, whose fragments every wave consumed before that barrier, one
+// DMA after every second MFMA of the second half (four in a row behind the barrier, each with
+// its 64-bit address, held the wave's MFMAs back: gate/up 976 x 22016 x 4096 in a stream of calls
+// 193.3 -> 188.3 us), whose first fragments of the next stage
+// are read before them.  At M = 976 the product is near what the chip sustains on these shapes: X in
+// fragment order, four waves of 128 x 128 (a third fewer LDS reads) and two K groups in a 128 x 128
+// block all measured the same or slower.  The DMA and
 // the waits are inline assembly because the compiler, which cannot tell LDS slots apart,
 // would otherwise wait for every DMA in flight before each LDS read.
 constexpr int DMA_NSTAGE = 5;
 
-// M0 is written with s_mov only: an SCC-writing instruction here would corrupt a compare the
-// compiler keeps live across the statement.
-#define ADT_DMA4(g0, g1, g2, g3, d)                                                                         \
-  asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off\n\t"                          \
-               "s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\t"                          \
-               "s_mov_b32 m0, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"                          \
-               "s_mov_b32 m0, %7\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, off" ::"v"(g0),                      \
-               "v"(g1), "v"(g2), "v"(g3), "s"(d), "s"((d) + 1024), "s"((d) + 2048), "s"((d) + 3072)          \
-               : "memory", "m0")
+// One DMA of 1 KB: lane l's 16 bytes from base + o to LDS byte d + 16 l.  M0 is written with s_mov
+// only: an SCC-writing instruction here would corrupt a compare the compiler keeps live across
+// the statement.
+__device__ __forceinline__ void dma_1k(uint32_t o, const char* base, uint32_t d) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o), "s"(base), "s"(d) : "memory", "m0");
+}
 
 // With ksplit > 1 the K stages of a block are split into ksplit contiguous ranges, one per
 // workgroup: range 0 writes C, range s > 0 writes the fp32 partial P[s-1] ([M][N], row stride
@@ -188,28 +190,32 @@ __global__ __launch_bounds__(WN * WM * WAVE) void gemm_nt_dma_kernel(const uint1
   constexpr int WAVES_W = (BN / 16) / 4;   // waves that load W tiles
   const int KTall = K / 32, kt0 = (int)((int64_t)KTall * ks / ksplit), kt1 = (int)((int64_t)KTall * (ks + 1) / ksplit);
 
-  // DMA sources: wave w fills tiles 4w..4w+3 of every stage (W tiles first, then X tiles)
-  const uint16_t* src[4];
+  // DMA sources: wave w fills tiles 4w..4w+3 of every stage (W tiles first, then X tiles), from
+  // a scalar base that advances with the stages and per-lane offsets that do not change
+  uint32_t off[4];
+  const char* sbase;
+  int64_t step;
+  if (wave < WAVES_W) {
+    sbase = (const char*)(W + ((int64_t)(n0 / 16 + 4 * wave) * (K / 32) + kt0) * 512);
+    step = 1024;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int T = 4 * wave + i;
-    if (wave < WAVES_W) {
-      src[i] = W + ((int64_t)(n0 / 16 + T) * (K / 32)) * 512 + lane * 8;
-    } else {
-      const int m = min(m0 + 16 * (T - BN / 16) + lane % 16, M - 1);   // rows past M feed discarded columns
-      src[i] = X + (int64_t)m * ldx + 8 * (lane / 16);
-    }
+    for (int i = 0; i < 4; ++i) off[i] = (uint32_t)i * (K / 32) * 1024 + lane * 16;
+  } else {
+    const int r0 = m0 + 16 * (4 * wave - BN / 16);
+    sbase = (const char*)(X + (int64_t)min(r0, M - 1) * ldx + (int64_t)kt0 * 32);
+    step = 64;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)   // rows past M feed discarded columns
+      off[i] = (uint32_t)(min(r0 + 16 * i + lane % 16, M - 1) - min(r0, M - 1)) * (uint32_t)(ldx * 2) + 16 * (lane / 16);
   }
-  const int64_t step = wave < WAVES_W ? 512 : 32;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) src[i] += kt0 * step;   // this workgroup's K range
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)lds;
   const uint32_t wdst = lds0 + 4 * wave * 1024;
   const int KT = kt1 - kt0;
-  auto issue = [&](int kt) {   // past the last stage: the last stage again, into a slot never read
-    const int64_t ks = min(kt, KT - 1) * step;
-    const uint32_t d = wdst + (kt % NSTAGE) * SLOT;
-    ADT_DMA4(src[0] + ks, src[1] + ks, src[2] + ks, src[3] + ks, d);
+  // tile i of stage kt; past the last stage: the last stage again, into a slot never read
+  auto issue1 = [&](int kt, int i) { dma_1k(off[i], sbase + min(kt, KT - 1) * step, wdst + (kt % NSTAGE) * SLOT + i * 1024); };
+  auto issue = [&](int kt) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) issue1(kt, i);
   };
   // fragment offsets (bytes) inside a slot: A = W rows wn*WTN + 32 nb + lane%32, B = X rows
   // wm*WTM + 32 mb + lane%32, columns 16 s + 8 (lane/32) of the stage
@@ -253,11 +259,19 @@ __global__ __launch_bounds__(WN * WM * WAVE) void gemm_nt_dma_kernel(const uint1
     __builtin_amdgcn_sched_group_barrier(0x008, NB * MB, 0);
     if constexpr (D == 3) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
-    issue(kt + D);
     frags(kt + 1, 0, a0, b0);   // past the last stage: a stale slot, never used
-    mma(a1, b1);
-    __builtin_amdgcn_sched_group_barrier(0x100, NB + MB, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, NB * MB, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < NB * MB; ++j) {
+      acc[j / MB][j % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[j / MB], b1[j % MB], acc[j / MB][j % MB], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (j == (i + 1) * NB * MB / 4 - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          issue1(kt + D, i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
   }
   // no DMA may still be writing this workgroup's LDS when it exits
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -278,7 +292,6 @@ __global__ __launch_bounds__(WN * WM * WAVE) void gemm_nt_dma_kernel(const uint1
       }
     }
 }
-#undef ADT_DMA4
 
 // C += P[0] + P[1] + ... in that order, four columns per thread.
 __global__ void gemm_nt_reduce_kernel(float* __restrict__ C, int64_t ldc, const float* __restrict__ P, int M, int N,
@@ -391,7 +404,9 @@ adt_status launch_gemm_nt(const void* X, int64_t ldx, const void* W, int64_t ldw
   // Packed weights in 256 x 256 (or 384 x 128) blocks when that gives at least 128
   // workgroups (half the CUs; measured faster than the 128 x 128 blocks down to there), or
   // with K split across workgroups: the DMA pipeline, as planned above.
-  if (packed && N % 256 == 0) {
+  // (its lanes' row offsets are 32-bit: rows of 16 MB and more take the register-staged kernel)
+  const bool dma = packed && ldx < (1 << 23);
+  if (dma && N % 256 == 0) {
     const NtPlan p = gemm_nt_plan(M, N, K, part ? part_elems : 0);
     if (p.bn == 384) {
       hipExtLaunchKernelGGL((gemm_nt_dma_kernel<384, 128, 4, 2, DMA_NSTAGE>),
@@ -414,7 +429,7 @@ adt_status launch_gemm_nt(const void* X, int64_t ldx, const void* W, int64_t ldw
   }
   // Packed weights with fewer blocks (the narrow projections of a batch of trees): 128 x 128
   // blocks of four waves through the same DMA pipeline, two workgroups per CU.
-  if (packed) {
+  if (dma) {
     const int ks = gemm_nt_ks128(M, N, K, part ? part_elems : 0);
     hipExtLaunchKernelGGL((gemm_nt_dma_kernel<128, 128, 2, 2, DMA_NSTAGE>), dim3((M + 127) / 128 * (N / 128) * ks),
                           dim3(4 * WAVE), 0, st, ev0, ks > 1 ? nullptr : ev1, 0, x, ldx, w, M, N, K, C, ldc, ks, part);
