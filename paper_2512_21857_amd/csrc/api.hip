@@ -1140,15 +1140,10 @@ extern "C" adt_status adt_device_check(void* stream) {
 }
 
 static adt_status set_root_only_tree(adt_session_s* s, int root_token, int L, hipStream_t st) {
-  int32_t v[1] = {1};
-  TRY(launch_set_i32(s->tr.n, small_of(v, 1), 1, st));
-  int32_t p[1] = {-1};
-  TRY(launch_set_i32(s->tr.parent, small_of(p, 1), 1, st));
-  int32_t t[1] = {root_token};
-  TRY(launch_set_i32(s->tr.token, small_of(t, 1), 1, st));
-  TRY(launch_tree_masks(s->tr.parent, s->tr.n, 1, R, s->tr.mask, s->tr.depth, st));
-  TRY(launch_tree_rows(s->tr.depth, s->tr.n, R, L, s->P, s->T, s->allowed_img, s->tr.pos, s->tr.allowed_rows,
-                       s->tr.score, st));
+  const int cell = std::min(std::max(L + 1 - s->P, 0), s->T - 1);   // of the root's successor
+  const TreeBufs& t = s->tr;
+  TRY(launch_root_tree(root_token, L, s->allowed_h[2 * cell], s->allowed_h[2 * cell + 1], R, t.n, t.parent, t.token,
+                       t.depth, t.pos, t.score, t.allowed_rows, t.mask, st));
   s->n_nodes = 1;
   s->expanded = false;
   return ADT_OK;
@@ -1173,10 +1168,9 @@ extern "C" adt_status adt_session_prefill(adt_session* s, const int32_t* prefix,
   for (int i = 0; i < nb * P; ++i)
     ADT_CHECK_ARG(prefix[i] >= 0 && prefix[i] < s->V, ADT_E_ARG, "prefill: id %d", prefix[i]);
   // ctok = the prompts of all branches, branch after branch
-  ADT_HIP(hipMemcpyAsync(s->ctok, prefix, sizeof(int32_t) * nb * P, hipMemcpyHostToDevice, st));
-  TRY(sync_stream(st));
-  TRY(launch_iota(s->cpos, P, 0, 1, st));
-  TRY(launch_chain_masks(s->cmask, P, st));
+  std::copy(prefix, prefix + nb * P, s->h_acc);   // pinned, at least 2 R >= nb P ids: no wait for the copy
+  ADT_HIP(hipMemcpyAsync(s->ctok, s->h_acc, sizeof(int32_t) * nb * P, hipMemcpyHostToDevice, st));
+  TRY(launch_prompt_rows(P, s->cpos, s->cfsrc, s->cmask, st));
   // Target and draft over the prompt in chunks of at most R rows (R / nb nodes).  Row p of the
   // draft takes the target feature of p - 1 (zeros for p = 0); the feature of the node before
   // a chunk is carried in draft-feature node 0.
@@ -1185,25 +1179,21 @@ extern "C" adt_status adt_session_prefill(adt_session* s, const int32_t* prefix,
     const int cn = std::min(CH, P - c0);
     const bool last = c0 + cn == P;
     TRY(target_forward(s, s->ctok + c0, cn, s->cpos + c0, c0, c0, cn, s->cmask, cn - 1, last ? 1 : 0, st, -1, P));
-    TRY(launch_iota(s->cfsrc, cn, -1, 1, st));
     if (c0 > 0) {
       int32_t carry[1] = {-2};
       TRY(launch_set_i32(s->cfsrc, small_of(carry, 1), 1, st));
     }
     TRY(draft_forward(s, s->ctok + c0, s->cfsrc, s->feat, cn, s->cpos + c0, c0, c0, cn, s->cmask, nullptr, 0, 0,
                       nullptr, nullptr, st, -1, P));
-    int32_t li[1] = {cn - 1};
-    TRY(launch_set_i32(s->idx, small_of(li, 1), 1, st));
-    TRY(launch_gather_rows(s->feat, s->idx, 1, nb * s->dm, last ? s->cfeat : s->dfeat, s->dt, st));
+    TRY(launch_gather_rows((const char*)s->feat + (size_t)(cn - 1) * nb * s->dm * esize(s->dt), nullptr, 1, nb * s->dm,
+                           last ? s->cfeat : s->dfeat, s->dt, st));
   }
-  TRY(set_root_only_tree(s, prefix[P - 1], P - 1, st));
-  // the root-only tree's successor is image cell 0
-  TRY(launch_fill_pairs(s->tr.allowed_rows, 1, s->allowed_h[0], s->allowed_h[1], st));
+  TRY(set_root_only_tree(s, prefix[P - 1], P - 1, st));   // its successor is image cell 0
   TRY(accept_impl(s->logits, s->V, s->V, s->tr.parent, s->tr.token, s->tr.allowed_rows, s->tr.n, 1, session_accept_cfg(s), 0,
                   s->tr.path, s->tr.nacc, s->tr.bonus, s->acc_ws, s->acc_ws_bytes, st));
-  int32_t first = 0;
-  ADT_HIP(hipMemcpyAsync(&first, s->tr.bonus, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  ADT_HIP(hipMemcpyAsync(s->h_acc + 2 * R + 1, s->tr.bonus, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   TRY(sync_stream(st));
+  const int32_t first = s->h_acc[2 * R + 1];
   s->tokens.assign(prefix, prefix + P);
   s->tokens.push_back(first);
   s->L = P;

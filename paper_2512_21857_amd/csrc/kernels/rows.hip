@@ -160,12 +160,12 @@ __global__ __launch_bounds__(ROW_THREADS) void draft_input_bf16_kernel(const uin
   }
 }
 
-// Rows of 16-byte pieces: dst[i] = src[idx[i]], every piece of a thread loaded before any store.
+// Rows of 16-byte pieces: dst[i] = src[idx[i]] (idx null: src[i]), every piece of a thread loaded before any store.
 __global__ __launch_bounds__(ROW_THREADS) void gather_rows16_kernel(const u16x8* __restrict__ src,
                                                                     const int32_t* __restrict__ idx, int pieces,
                                                                     u16x8* __restrict__ dst) {
   const int i = blockIdx.x;
-  const u16x8* s = src + (int64_t)idx[i] * pieces;
+  const u16x8* s = src + (int64_t)(idx ? idx[i] : i) * pieces;
   u16x8* o = dst + (int64_t)i * pieces;
   for (int c0 = 0; c0 < pieces; c0 += 4 * ROW_THREADS) {
     u16x8 v[4];
@@ -406,12 +406,12 @@ __global__ __launch_bounds__(ROW_THREADS) void swiglu_kernel(const float* __rest
   Elem<T>::store(o, 3, g.w / (1.f + expf(-g.w)) * u.w);
 }
 
-// dst[i] = src[idx[i]] for i < cnt (rows of length d, element type T).
+// dst[i] = src[idx[i]] (idx null: src[i]) for i < cnt (rows of length d, element type T).
 template <typename T>
 __global__ void gather_rows_kernel(const T* __restrict__ src, const int32_t* __restrict__ idx, int d,
                                    T* __restrict__ dst) {
   const int i = blockIdx.x;
-  const T* s = src + (int64_t)idx[i] * d;
+  const T* s = src + (int64_t)(idx ? idx[i] : i) * d;
   for (int c = threadIdx.x; c < d; c += blockDim.x) dst[(int64_t)i * d + c] = s[c];
 }
 

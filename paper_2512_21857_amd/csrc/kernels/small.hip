@@ -16,13 +16,33 @@ __global__ void fill_pairs_kernel(int32_t* dst, int rows, int lo, int hi) {
   }
 }
 
-__global__ void iota_kernel(int32_t* dst, int count, int start, int step) {
-  for (int i = threadIdx.x; i < count; i += blockDim.x) dst[i] = start + i * step;
+// The tree of a root alone, whose successor may be any id of [lo, hi): every array of the tree in
+// one launch (six small ones had taken 24 us of a prefill).
+__global__ void root_tree_kernel(int token_id, int L, int lo, int hi, int n_max, int32_t* n, int32_t* parent,
+                                 int32_t* token, int32_t* depth, int32_t* pos, float* score, int32_t* allowed_rows,
+                                 uint64_t* mask) {
+  for (int i = threadIdx.x; i < n_max; i += blockDim.x) {
+    mask[i * 2] = i == 0 ? 1 : 0;
+    mask[i * 2 + 1] = 0;
+    depth[i] = 0;
+  }
+  if (threadIdx.x == 0) {
+    *n = 1;
+    parent[0] = -1;
+    token[0] = token_id;
+    pos[0] = L;
+    score[0] = 0.f;
+    allowed_rows[0] = lo;
+    allowed_rows[1] = hi;
+  }
 }
 
-// Masks of a chain (causal block): row i has bits 0..i.
-__global__ void chain_masks_kernel(uint64_t* mask, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+// Rows of a prompt of P tokens: positions 0.., the masks of a chain, and for the draft the feature of
+// the row before (none for row 0).
+__global__ void prompt_rows_kernel(int P, int32_t* pos, int32_t* fsrc, uint64_t* mask) {
+  for (int i = threadIdx.x; i < P; i += blockDim.x) {
+    pos[i] = i;
+    fsrc[i] = i - 1;
     const int b = i + 1;
     mask[i * 2] = b >= 64 ? ~0ull : ((1ull << b) - 1);
     mask[i * 2 + 1] = b <= 64 ? 0ull : (b >= 128 ? ~0ull : ((1ull << (b - 64)) - 1));
@@ -66,13 +86,15 @@ adt_status launch_fill_pairs(int32_t* dst, int rows, int lo, int hi, hipStream_t
   ADT_LAUNCH_CHECK();
   return ADT_OK;
 }
-adt_status launch_iota(int32_t* dst, int count, int start, int step, hipStream_t st) {
-  iota_kernel<<<1, 128, 0, st>>>(dst, count, start, step);
+adt_status launch_root_tree(int token_id, int L, int lo, int hi, int n_max, int32_t* n, int32_t* parent, int32_t* token,
+                            int32_t* depth, int32_t* pos, float* score, int32_t* allowed_rows, uint64_t* mask,
+                            hipStream_t st) {
+  root_tree_kernel<<<1, 128, 0, st>>>(token_id, L, lo, hi, n_max, n, parent, token, depth, pos, score, allowed_rows, mask);
   ADT_LAUNCH_CHECK();
   return ADT_OK;
 }
-adt_status launch_chain_masks(uint64_t* mask, int n, hipStream_t st) {
-  chain_masks_kernel<<<1, 128, 0, st>>>(mask, n);
+adt_status launch_prompt_rows(int P, int32_t* pos, int32_t* fsrc, uint64_t* mask, hipStream_t st) {
+  prompt_rows_kernel<<<1, 128, 0, st>>>(P, pos, fsrc, mask);
   ADT_LAUNCH_CHECK();
   return ADT_OK;
 }

@@ -244,8 +244,10 @@ adt_status launch_accept_greedy(const int32_t* argmax, int kmax, const int32_t* 
 adt_status launch_set_i32(int32_t* dst, const SmallI32& vals, int count, hipStream_t st);
 adt_status launch_fill_pairs(int32_t* dst, int rows, int lo, int hi, hipStream_t st);
 adt_status launch_table_rows(const int32_t* tok, int count, int depth, int rows, int32_t* idx, hipStream_t st);
-adt_status launch_iota(int32_t* dst, int count, int start, int step, hipStream_t st);
-adt_status launch_chain_masks(uint64_t* mask, int n, hipStream_t st);
+adt_status launch_root_tree(int token_id, int L, int lo, int hi, int n_max, int32_t* n, int32_t* parent, int32_t* token,
+                            int32_t* depth, int32_t* pos, float* score, int32_t* allowed_rows, uint64_t* mask,
+                            hipStream_t st);
+adt_status launch_prompt_rows(int P, int32_t* pos, int32_t* fsrc, uint64_t* mask, hipStream_t st);
 adt_status launch_tree_rows(const int32_t* depth, const int32_t* n_nodes, int n_max, int L, int P, int n_image,
                             const int32_t* allowed_img, int32_t* pos, int32_t* allowed_rows, float* score,
                             hipStream_t st);
