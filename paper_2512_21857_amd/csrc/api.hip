@@ -1007,23 +1007,34 @@ static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t*
     TRY(capt_snap(s, 2 * (l1 - l0), st));
     return ADT_OK;
   }
-  // fp32: products into part, row kernels finish each step
+  // fp32: as above with the residual rows themselves as the normalised products' inputs; QKV goes
+  // through part to RoPE and the cache, and the last down product to the final norm
+  GemmEpi norm, add;
+  norm.norm_eps = eps;
+  norm.norm = true;
+  add.mode = EPI_RESID;
+  add.resid = s->h;
   for (int l = l0; l < l1; ++l) {
     char* kc = draft ? (char*)s->d.dk_cache : (char*)s->d.k_cache + (size_t)l * H * stride_h * es;
     char* vc = draft ? (char*)s->d.dv_cache : (char*)s->d.v_cache + (size_t)l * H * stride_h * es;
     TRY(capt_snap(s, 2 * (l - l0), st));
-    TRY(gemm_p(s->act, dm, m->qkv[l], rows, 3 * dm, dm, dt, s->part, st));
+    TRY(gemm_p(s->h, dm, m->qkv[l], rows, 3 * dm, dm, dt, s->part, st, norm));
     TRY(launch_qkv_rope(s->part, 1, rows, H, Dh, pos, s->scal + SC_SLOT, s->rope, s->q, kc, vc, stride_h, dt, st, br));
     TRY(attention(kc, vc));
-    TRY(gemm_p(s->att, dm, m->o[l], rows, dm, dm, dt, s->part, st));
-    TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, s->act, dt, st));
+    TRY(gemm_p(s->att, dm, m->o[l], rows, dm, dm, dt, s->part, st, add));
     TRY(capt_snap(s, 2 * (l - l0) + 1, st));
     GemmEpi sw;
     sw.mode = EPI_SWIGLU;
     sw.out = (float*)s->sw;
-    TRY(gemm_p(s->act, dm, m->gu[l], rows, 2 * F, dm, dt, s->part, st, sw));
+    sw.norm_eps = eps;
+    sw.norm = true;
+    TRY(gemm_p(s->h, dm, m->gu[l], rows, 2 * F, dm, dt, s->part, st, sw));
+    if (l + 1 < l1 || !final_out) {
+      TRY(gemm_p(s->sw, F, m->down[l], rows, dm, F, dt, s->part, st, add));
+      continue;
+    }
     TRY(gemm_p(s->sw, F, m->down[l], rows, dm, F, dt, s->part, st));
-    TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, l + 1 == l1 ? final_out : s->act, dt, st));
+    TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, final_out, dt, st));
   }
   return capt_snap(s, 2 * (l1 - l0), st);
 }
@@ -1058,10 +1069,10 @@ static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, co
                                  int64_t key = -1, int tok_boff = 0) {
   const int pk = act_blocks(s, s->nb * M);
   // The embedding rows and, in the same launch, the scalars that change from call to call (outside
-  // the graph for their sake; a launch of their own took 2-4.6 us).  bf16: act takes the raw
-  // embedding rows (the first projection normalises them).
+  // the graph for their sake; a launch of their own took 2-4.6 us).  act takes the raw
+  // embedding rows (bf16: the first projection normalises them; fp32 reads the residual itself).
   TRY(launch_embed_norm(s->m->d.embed, tok, s->nb * M, s->dm, s->m->d.norm_eps, s->h, s->act, s->dt, st,
-                        Branches{s->nb, tok_boff, 0}, pk, pk > 0, FwdScalars{s->scal, L_pre, M, n_tail, slot0}));
+                        Branches{s->nb, tok_boff, 0}, pk, true, FwdScalars{s->scal, L_pre, M, n_tail, slot0}));
   auto body = [&](hipStream_t cs) -> adt_status {
     TRY(capt_begin(s, false, M, L_pre, slot0, n_tail, tok, pos, mask, cs));
     // logits of every row read the final norm from act in the fragment layout
@@ -1098,8 +1109,11 @@ static adt_status draft_forward(adt_session_s* s, const int32_t* tok, const int3
     if (dt == ADT_BF16) {
       TRY(resid_proj(s, s->xin, s->m->d.draft_fc, rows, 2 * dm, 1, cs));
     } else {
-      TRY(gemm_p(s->xin, 2 * dm, s->m->d.draft_fc, rows, dm, 2 * dm, dt, s->part, cs));
-      TRY(launch_add_norm(s->part, 1, rows, dm, 1, s->m->d.norm_eps, s->h, s->act, dt, cs));
+      GemmEpi e;
+      e.mode = EPI_RESID;
+      e.resid = s->h;
+      e.assign = 1;
+      TRY(gemm_p(s->xin, 2 * dm, s->m->d.draft_fc, rows, dm, 2 * dm, dt, s->part, cs, e));
     }
     const bool all = pk && fout && lm_row0 == 0 && lm_rows == M;
     TRY(run_layers(s, true, M, pos, slot0, L_pre, n_tail, mask, fout, all, cs));

@@ -546,14 +546,19 @@ __global__ __launch_bounds__(TILE_THREADS, 2) void gemm_rows_dma_kernel(const ui
 // sums stay as short as a lane-strided sum's); accumulators, then waves, are added pairwise.  One wave per column with the rows read one by one had taken 24-72 us a
 // launch at 17 rows (K 256 and 1024): 377 -> 104 us for the two-layer model's 17-row forward.
 // W and X rows need 4-byte alignment only; K is a multiple of 16; rows past M or N repeat the last.
-// With act the gate/up product stores silu(gate) up there instead (a launch of its own took 2.5 us).
+// Epilogues as in the bf16 path, each instead of a launch of 2.5-5 us: act takes silu(gate) up of the
+// gate/up product, resid is added to (assign: set), and with NORM the rows are un-normalised
+// and scaled afterwards by their RMSNorm factor, whose sum of squares the waves take from the
+// fragments they multiply (two-layer tiny model's 17-row forward 80.4 -> 75.1 us).
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int MR, int U>
+template <int MR, int U, bool NORM>
 __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ X, int ldx,
                                                                 const float* __restrict__ W, int M, int N, int K,
-                                                                float* __restrict__ part, float* __restrict__ act) {
+                                                                float* __restrict__ part, float* __restrict__ act,
+                                                                float* __restrict__ resid, int assign, float eps) {
   __shared__ f32x4 red[TILE_WAVES][MR][WAVE];
+  __shared__ float red_ss[NORM ? TILE_WAVES : 1][NORM ? MR : 1][16];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int lane = threadIdx.x % WAVE, lq = lane & 15, g = lane >> 4;
   const int n0 = blockIdx.x * 16, m0 = blockIdx.y * MR * 16;
@@ -572,6 +577,7 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __r
   for (int m = 0; m < MR; ++m)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[m][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float ss[MR][2] = {};
   for (int c = s0; c < s1; c += U) {
     f32x4 w[U], x[U][MR];
 #pragma unroll
@@ -589,6 +595,23 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __r
         for (int m = 0; m < MR; ++m)
           acc[m][u % 2 * 4 + e] =
               __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e], x[u][m][e], acc[m][u % 2 * 4 + e], 0, 0, 0);
+    if (NORM) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int m = 0; m < MR; ++m)
+          ss[m][u % 2] += (x[u][m][0] * x[u][m][0] + x[u][m][1] * x[u][m][1]) +
+                          (x[u][m][2] * x[u][m][2] + x[u][m][3] * x[u][m][3]);
+    }
+  }
+  if (NORM) {
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      float v = ss[m][0] + ss[m][1];
+      v += __shfl_xor(v, 16, WAVE);
+      v += __shfl_xor(v, 32, WAVE);
+      if (g == 0) red_ss[wave][m][lq] = v;
+    }
   }
 #pragma unroll
   for (int m = 0; m < MR; ++m) {
@@ -610,8 +633,15 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __r
       for (int w = 0; w < TILE_WAVES; w += 2 * h)
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[w][r] += v[w + h][r];
-    const f32x4 y = v[0];
+    f32x4 y = v[0];
     const int row = m0 + wave * 16 + lq, n = n0 + 4 * g;
+    if (NORM) {
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < TILE_WAVES; ++w) t += red_ss[w][wave][lq];
+      const float r = rsqrtf(t / K + eps);
+      y = f32x4{y[0] * r, y[1] * r, y[2] * r, y[3] * r};
+    }
     if (act) {   // gate columns in lanes g < 2, the up columns that match them in lanes g + 2
       const f32x4 u = shfl_xor4(y, 32);
       if (row < M && g < 2 && n < N)
@@ -619,7 +649,17 @@ __global__ __launch_bounds__(TILE_THREADS) void gemm_f32_kernel(const float* __r
             f32x4{y[0] / (1.f + expf(-y[0])) * u[0], y[1] / (1.f + expf(-y[1])) * u[1],
                   y[2] / (1.f + expf(-y[2])) * u[2], y[3] / (1.f + expf(-y[3])) * u[3]};
     } else if (row < M) {
-      float* dst = part + (int64_t)row * N + n;
+      float* dst = (resid ? resid : part) + (int64_t)row * N + n;
+      if (resid && !assign) {
+        if (n + 4 <= N) {
+          const f32x4 h = *reinterpret_cast<const f32x4_a4*>(dst);
+          y = f32x4{h[0] + y[0], h[1] + y[1], h[2] + y[2], h[3] + y[3]};
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (n + r < N) y[r] += dst[r];
+        }
+      }
       if (n + 4 <= N) {
         *reinterpret_cast<f32x4_a4*>(dst) = y;
       } else {
@@ -801,13 +841,21 @@ adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int
     const float *x = (const float*)X, *w = (const float*)Wp;
     float* act = epi.mode == EPI_SWIGLU ? epi.out : nullptr;
     ADT_CHECK_ARG(epi.mode != EPI_SWIGLU || (act && N % 16 == 0), ADT_E_ARG, "gemm f32: SwiGLU output of N=%d", N);
-#define ADT_GF(MRV, UV)                                                                                               \
-  hipExtLaunchKernelGGL((gemm_f32_kernel<MRV, UV>), dim3(tiles, (mb + MRV - 1) / MRV), dim3(TILE_THREADS), 0, st, ev0, \
-                        ev1, 0, x, ldx, w, M, N, K, part, act)
-    if ((int64_t)tiles * mb <= 512) ADT_GF(1, 8);
-    else if ((int64_t)tiles * mb <= 1024) ADT_GF(2, 4);
-    else ADT_GF(4, 4);
+    float* resid = epi.mode == EPI_RESID ? epi.resid : nullptr;
+    ADT_CHECK_ARG(epi.mode != EPI_RESID || resid, ADT_E_ARG, "gemm f32: residual rows");
+#define ADT_GF_L(MRV, UV, NV)                                                                                        \
+  hipExtLaunchKernelGGL((gemm_f32_kernel<MRV, UV, NV>), dim3(tiles, (mb + MRV - 1) / MRV), dim3(TILE_THREADS), 0, st, \
+                        ev0, ev1, 0, x, ldx, w, M, N, K, part, act, resid, epi.assign, epi.norm_eps)
+#define ADT_GF(MRV, UV)                        \
+  {                                            \
+    if (epi.norm) ADT_GF_L(MRV, UV, true);     \
+    else ADT_GF_L(MRV, UV, false);             \
+  }
+    if ((int64_t)tiles * mb <= 512) ADT_GF(1, 8)
+    else if ((int64_t)tiles * mb <= 1024) ADT_GF(2, 4)
+    else ADT_GF(4, 4)
 #undef ADT_GF
+#undef ADT_GF_L
     ADT_LAUNCH_CHECK();
     if (splits) *splits = 1;
     return ADT_OK;

@@ -131,6 +131,7 @@ struct GemmEpi {
   // output row is scaled by 1 / sqrt(mean of its input row's squares + norm_eps), the RMSNorm
   // (unit gain) of the bf16 rows the kernel reads
   float norm_eps = 0.f;
+  bool norm = false;   // fp32 products: the norm whatever norm_eps is
 };
 struct RowsPlan {
   int T, S;       // at most T 16-column tiles per workgroup, S K ranges
