@@ -11,7 +11,7 @@
 // Three kernels by shape: tree_attn_blk_kernel (trees of 17-128 rows over many pairs, in a
 // work-balanced sequence order, and every tree over few pairs: one workgroup per pair, or
 // per pair and key split, sharing each K/V block through LDS; splits write (O, m, l)
-// partials that tree_attn_combine_kernel merges with log-sum-exp weights),
+// partials that the last split to arrive, or tree_attn_combine_kernel, merges with log-sum-exp weights),
 // tree_attn_wg_kernel (trees of at most 16 rows over many pairs: one workgroup per pair
 // whose waves split the keys and merge in LDS), and tree_attn_f32_kernel.
 #include <hip/hip_ext.h>

@@ -143,13 +143,13 @@ __global__ __launch_bounds__(NT_THREADS) void gemm_nt_kernel(const uint16_t* __r
 // Pipeline, per stage kt: the fragments of the stage's second half are read while the first
 // half's eight MFMAs run; each wave waits for its own DMA of stage kt+1 (the NSTAGE-3 newer
 // stages stay in flight) and one barrier publishes it; the DMA of stage kt+NSTAGE-1 then
-// refills the slot of stage kt-1, whose fragments every wave consumed before that barrier, one
-// DMA after every second MFMA of the second half (four in a row behind the barrier, each with
-// its 64-bit address, held the wave's MFMAs back: gate/up 976 x 22016 x 4096 in a stream of calls
-// 193.3 -> 188.3 us), whose first fragments of the next stage
-// are read before them.  At M = 976 the product is near what the chip sustains on these shapes: X in
-// fragment order, four waves of 128 x 128 (a third fewer LDS reads) and two K groups in a 128 x 128
-// block all measured the same or slower.  The DMA and
+// refills the slot of stage kt-1, whose fragments every wave consumed before that barrier; the
+// next stage's first fragments are read while the second half's MFMAs run.  One DMA tile is
+// issued after every second of those MFMAs, from a scalar base: four in a row behind the barrier,
+// each with a 64-bit lane address, held the wave's MFMAs back (976 x 22016 x 4096 in a stream of
+// calls 193.3 -> 188.3 us).  At M = 976 all of these measured the same or slower: X in fragment
+// order, four waves of 128 x 128 (a third fewer LDS reads), two K groups in a 128 x 128 block; a
+// library product of the same operands takes 197.5 us (bf16 result).  The DMA and
 // the waits are inline assembly because the compiler, which cannot tell LDS slots apart,
 // would otherwise wait for every DMA in flight before each LDS read.
 constexpr int DMA_NSTAGE = 5;
