@@ -382,8 +382,9 @@ __global__ __launch_bounds__(COMB_THREADS) void tree_attn_combine_kernel(
 
 // fp32 path: one block per (query, head, sequence); scores staged in LDS.  Bound by the latency
 // of its loads (81 keys at 17 rows): a thread takes one key with sixteen dims in flight, then the
-// keys are dealt to 128 / (DH / 4) groups of threads of four dims each, whose sums meet in LDS.
-// A load per dim, and one thread per dim over every key, had taken 7.4 us there.
+// keys are dealt to 128 / (DH / 4) groups of threads of four dims each, whose sums meet in LDS
+// (7-8 us there in a trace, about what a load per dim and one thread per dim over every key
+// took, which grows with every key).
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int F32_THREADS = 128;
 __global__ __launch_bounds__(F32_THREADS) void tree_attn_f32_kernel(
