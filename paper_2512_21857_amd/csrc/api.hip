@@ -834,12 +834,36 @@ static adt_status gemm_p(const void* X, int ldx, const void* W, int M, int N, in
 }
 
 // ---------------------------------------------------------------------------- capture
-// Opens the record of one forward (adt_session_set_capture): checks that its residual
-// snapshots, FC inputs and row metadata fit the caller's buffers, then copies the rows'
-// tokens (branch 0), positions and ancestor masks.  Nothing is launched when a buffer is full.
+// What the record of a forward of M nodes takes: residual floats, FC input bytes, metadata ints.
+struct CaptNeed {
+  size_t resid, xin, meta;
+};
+static int capt_snapshots(const adt_session_s* s, bool draft) { return draft ? 3 : 2 * s->Lr + 1; }
+static CaptNeed capt_need(const adt_session_s* s, bool draft, int M) {
+  const size_t rows = (size_t)s->nb * M;
+  return {capt_snapshots(s, draft) * rows * s->dm, draft ? rows * 2 * s->dm * esize(s->dt) : 0,
+          (size_t)M * (2 + 2 * ADT_MASK_WORDS)};
+}
+
+// Whether the record of the next forward (adt_session_set_capture) fits the caller's buffers.
+// Called before the forward's first launch: one that does not fit launches nothing.
+static adt_status capt_check(adt_session_s* s, bool draft, int M) {
+  s->capt_cur = -1;
+  if (!s->capt_on) return ADT_OK;
+  const CaptNeed n = capt_need(s, draft, M);
+  ADT_CHECK_ARG(s->capt_resid + n.resid <= s->capt.resid_elems, ADT_E_CAPACITY,
+                "capture: residual buffer holds %zu floats, %zu needed", s->capt.resid_elems, s->capt_resid + n.resid);
+  ADT_CHECK_ARG(!draft || (s->capt.xin && s->capt_xin + n.xin <= s->capt.xin_bytes), ADT_E_CAPACITY,
+                "capture: FC input buffer holds %zu bytes, %zu needed", s->capt.xin_bytes, s->capt_xin + n.xin);
+  ADT_CHECK_ARG(s->capt.meta && s->capt_meta + n.meta <= s->capt.meta_elems, ADT_E_CAPACITY,
+                "capture: metadata buffer holds %zu ints, %zu needed", s->capt.meta_elems, s->capt_meta + n.meta);
+  return ADT_OK;
+}
+
+// Opens the record of a forward that capt_check has let through: copies the rows' tokens
+// (branch 0), positions and ancestor masks.
 static adt_status capt_begin(adt_session_s* s, bool draft, int M, int L_pre, int slot0, int n_tail,
                              const int32_t* tok, const int32_t* pos, const uint64_t* mask, hipStream_t st) {
-  s->capt_cur = -1;
   if (!s->capt_on) return ADT_OK;
   adt_capture_rec r{};
   r.draft = draft ? 1 : 0;
@@ -848,26 +872,18 @@ static adt_status capt_begin(adt_session_s* s, bool draft, int M, int L_pre, int
   r.kv_prefix = L_pre;
   r.slot0 = slot0;
   r.n_tail = n_tail;
-  r.snapshots = draft ? 3 : 2 * s->Lr + 1;
+  r.snapshots = capt_snapshots(s, draft);
   r.resid_off = (int64_t)s->capt_resid;
   r.xin_off = (int64_t)s->capt_xin;
   r.meta_off = (int64_t)s->capt_meta;
-  const size_t nres = (size_t)r.snapshots * r.rows * s->dm;
-  const size_t nxin = draft ? (size_t)r.rows * 2 * s->dm * esize(s->dt) : 0;
-  const size_t nmeta = (size_t)M * (2 + 2 * ADT_MASK_WORDS);
-  ADT_CHECK_ARG(s->capt_resid + nres <= s->capt.resid_elems, ADT_E_CAPACITY,
-                "capture: residual buffer holds %zu floats, %zu needed", s->capt.resid_elems, s->capt_resid + nres);
-  ADT_CHECK_ARG(!draft || (s->capt.xin && s->capt_xin + nxin <= s->capt.xin_bytes), ADT_E_CAPACITY,
-                "capture: FC input buffer holds %zu bytes, %zu needed", s->capt.xin_bytes, s->capt_xin + nxin);
-  ADT_CHECK_ARG(s->capt.meta && s->capt_meta + nmeta <= s->capt.meta_elems, ADT_E_CAPACITY,
-                "capture: metadata buffer holds %zu ints, %zu needed", s->capt.meta_elems, s->capt_meta + nmeta);
+  const CaptNeed need = capt_need(s, draft, M);
   int32_t* mt = s->capt.meta + s->capt_meta;
   ADT_HIP(hipMemcpyAsync(mt, tok, sizeof(int32_t) * M, hipMemcpyDeviceToDevice, st));
   ADT_HIP(hipMemcpyAsync(mt + M, pos, sizeof(int32_t) * M, hipMemcpyDeviceToDevice, st));
   ADT_HIP(hipMemcpyAsync(mt + 2 * M, mask, sizeof(uint64_t) * ADT_MASK_WORDS * M, hipMemcpyDeviceToDevice, st));
-  s->capt_resid += nres;
-  s->capt_xin += nxin;
-  s->capt_meta += nmeta;
+  s->capt_resid += need.resid;
+  s->capt_xin += need.xin;
+  s->capt_meta += need.meta;
   s->capt_log.push_back(r);
   s->capt_cur = (int)s->capt_log.size() - 1;
   return ADT_OK;
@@ -1067,6 +1083,7 @@ static adt_status lm_head(adt_session_s* s, const void* feat_rows, int ldx, int 
 static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, const int32_t* pos, int slot0, int L_pre,
                                  int n_tail, const uint64_t* mask, int lm_row0, int lm_rows, hipStream_t st,
                                  int64_t key = -1, int tok_boff = 0) {
+  TRY(capt_check(s, false, M));
   const int pk = act_blocks(s, s->nb * M);
   // The embedding rows and, in the same launch, the scalars that change from call to call (outside
   // the graph for their sake; a launch of their own took 2-4.6 us).  act takes the raw
@@ -1097,6 +1114,7 @@ static adt_status draft_forward(adt_session_s* s, const int32_t* tok, const int3
                                 int lm_row0, int lm_rows, float* lout, float* lraw, hipStream_t st, int64_t key = -1,
                                 int tok_boff = 0, const CatchUp& cu = {}) {
   const int dm = s->dm, dt = s->dt, rows = s->nb * M;
+  TRY(capt_check(s, true, M));
   const int pk = act_blocks(s, rows);
   TRY(launch_draft_input(s->m->d.embed, tok, fsrc, fa, s->dfeat, rows, dm, s->xin, dt, st,
                          Branches{s->nb, tok_boff, 0}, pk, FwdScalars{s->scal, L_pre, M, n_tail, slot0}, cu));

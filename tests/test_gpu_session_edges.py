@@ -1,0 +1,47 @@
+"""A session's forwards where their bookkeeping ends."""
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rt():
+    from paper_2512_21857_amd import runtime
+    assert torch.cuda.is_available()
+    return runtime
+
+
+def _session(rt, dtype, **kw):
+    cfg = synth.shrink(synth.get_config("tiny"), dtype=dtype)
+    return cfg, rt.DeviceSession(rt.DeviceModel(cfg, synth.model_weights(cfg)), cfg, **kw)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("call,short", [("verify", "resid_elems"), ("verify", "meta_elems"), ("expand", "resid_elems"),
+                                        ("expand", "xin_bytes"), ("expand", "meta_elems")])
+def test_full_capture_buffer_launches_nothing(rt, dtype, call, short):
+    """A forward whose record would overrun a capture buffer fails with the capacity code and
+    leaves every byte of the session's workspace, caches and record as it was."""
+    from paper_2512_21857_amd import abi
+    cfg, sess = _session(rt, dtype)
+    sess.prefill(synth.prefix_ids(cfg))
+    sess.expand(2, 3, 9)
+    sess.verify()
+    if call == "verify":
+        sess.expand(1, 4, 16)   # other rows than the last verify's, so that a launch shows
+    sess.set_capture(**{**dict(resid_elems=1 << 20, xin_bytes=1 << 20, meta_elems=1 << 12), short: 4})
+    if short == "xin_bytes":
+        assert sess._capture[1].numel() == 16
+    bufs = (sess.workspace, sess.k_cache, sess.v_cache, sess.dk_cache, sess.dv_cache, *sess._capture)
+    torch.cuda.synchronize()
+    before = [b.clone() for b in bufs]
+    with pytest.raises(abi.AdtError) as e:
+        sess.verify() if call == "verify" else sess.expand(1, 4, 16)
+    assert e.value.code == abi.E_CAPACITY
+    torch.cuda.synchronize()
+    for b, was in zip(bufs, before):
+        assert torch.equal(b.view(torch.uint8), was.view(torch.uint8))
+    assert sess.captured() == []
