@@ -391,7 +391,8 @@ typedef struct {
   int32_t* path; int32_t* n_acc; int32_t* bonus;  /* last acceptance */
   const int32_t* tokens_host;   /* [host] committed ids */
   /* scratch of the last forward (last layer run): rotated queries [rows][d] dtype, attention
-   * output [rows][d] dtype, normed activations [rows][d] dtype, residual stream [rows][d] fp32.
+   * output [rows][d] dtype, normed activations [rows][d] dtype (f32 sessions: the last layer's
+   * MLP input), residual stream [rows][d] fp32.
    * In bf16 sessions act holds the bf16 residual rows (each projection applies its RMSNorm
    * itself) except after a forward's last layer, where it holds the final norm; att and act
    * are then in the fragment layout of the projections' inputs: with

@@ -1024,7 +1024,8 @@ static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t*
     return ADT_OK;
   }
   // fp32: as above with the residual rows themselves as the normalised products' inputs; QKV goes
-  // through part to RoPE and the cache, and the last down product to the final norm
+  // through part to RoPE and the cache, and the last down product to the final norm, which also
+  // leaves the last layer's normed MLP input in act (the session's view shows it)
   GemmEpi norm, add;
   norm.norm_eps = eps;
   norm.norm = true;
@@ -1045,12 +1046,12 @@ static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t*
     sw.norm_eps = eps;
     sw.norm = true;
     TRY(gemm_p(s->h, dm, m->gu[l], rows, 2 * F, dm, dt, s->part, st, sw));
-    if (l + 1 < l1 || !final_out) {
+    if (l + 1 < l1) {
       TRY(gemm_p(s->sw, F, m->down[l], rows, dm, F, dt, s->part, st, add));
       continue;
     }
     TRY(gemm_p(s->sw, F, m->down[l], rows, dm, F, dt, s->part, st));
-    TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, final_out, dt, st));
+    TRY(launch_add_norm(s->part, 1, rows, dm, 0, eps, s->h, final_out, dt, st, s->act));
   }
   return capt_snap(s, 2 * (l1 - l0), st);
 }
@@ -1086,10 +1087,11 @@ static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, co
   TRY(capt_check(s, false, M));
   const int pk = act_blocks(s, s->nb * M);
   // The embedding rows and, in the same launch, the scalars that change from call to call (outside
-  // the graph for their sake; a launch of their own took 2-4.6 us).  act takes the raw
-  // embedding rows (bf16: the first projection normalises them; fp32 reads the residual itself).
-  TRY(launch_embed_norm(s->m->d.embed, tok, s->nb * M, s->dm, s->m->d.norm_eps, s->h, s->act, s->dt, st,
-                        Branches{s->nb, tok_boff, 0}, pk, true, FwdScalars{s->scal, L_pre, M, n_tail, slot0}));
+  // the graph for their sake; a launch of their own took 2-4.6 us).  bf16: act takes the
+  // raw embedding rows, which the first projection normalises; fp32 products read the residual itself.
+  TRY(launch_embed_norm(s->m->d.embed, tok, s->nb * M, s->dm, s->m->d.norm_eps, s->h,
+                        s->dt == ADT_BF16 ? s->act : nullptr, s->dt, st, Branches{s->nb, tok_boff, 0}, pk, true,
+                        FwdScalars{s->scal, L_pre, M, n_tail, slot0}));
   auto body = [&](hipStream_t cs) -> adt_status {
     TRY(capt_begin(s, false, M, L_pre, slot0, n_tail, tok, pos, mask, cs));
     // logits of every row read the final norm from act in the fragment layout

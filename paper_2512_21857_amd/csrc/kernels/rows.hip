@@ -14,7 +14,7 @@ constexpr int ROW_THREADS = 256;
 ADT_DEVICE_ERROR_WORD(rows)
 
 // h[m] = E[tok[m]] (fp32 residual), a[m] = RMSNorm(h[m]) (raw: h[m] itself) in dtype T
-// (layout a_pk).
+// (layout a_pk), or with a null nothing.
 template <typename T>
 __global__ __launch_bounds__(ROW_THREADS) void embed_norm_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok,
                                                                  int d, float eps, float* __restrict__ h,
@@ -30,6 +30,7 @@ __global__ __launch_bounds__(ROW_THREADS) void embed_norm_kernel(const T* __rest
     h[(int64_t)m * d + i] = v;
     ss += v * v;
   }
+  if (!a) return;
   const float r = raw ? 1.f : rsqrtf(block_sum(ss, red) / d + eps);
   for (int i = threadIdx.x; i < d; i += blockDim.x)
     Elem<T>::store(a, act_index(m, i, d, a_pk), h[(int64_t)m * d + i] * r);
@@ -259,17 +260,18 @@ __device__ __forceinline__ float4 sum_parts4(const float* __restrict__ part, int
   return y;
 }
 
-// y = sum_s part[s][m][:]; h[m] = (assign ? y : h[m] + y); if a: a[m] = RMSNorm(h[m]).
+// y = sum_s part[s][m][:]; h[m] = (assign ? y : h[m] + y); if a: a[m] = RMSNorm(h[m]); if before
+// (not with assign): before[m] = RMSNorm of h[m] as it was.
 // One block per row, four columns per thread (d % 4 == 0, d <= 4 * blockDim.x * 4).
 template <typename T>
 __global__ __launch_bounds__(1024) void add_norm_kernel(const float* __restrict__ part, int splits, int M, int d,
                                                         int assign, float eps, float* __restrict__ h,
-                                                        T* __restrict__ a) {
-  __shared__ float red[16];
+                                                        T* __restrict__ a, T* __restrict__ before) {
+  __shared__ float red[32];
   const int m = blockIdx.x;
   const int64_t stride = (int64_t)M * d;
-  float4 hv[4];
-  float ss = 0.f;
+  float4 hv[4], ov[4];
+  float ss = 0.f, so = 0.f;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int c = (threadIdx.x + it * blockDim.x) * 4;
@@ -279,25 +281,47 @@ __global__ __launch_bounds__(1024) void add_norm_kernel(const float* __restrict_
       if (!assign) {
         const float4 o = *reinterpret_cast<const float4*>(h + (int64_t)m * d + c);
         v = make_float4(o.x + y.x, o.y + y.y, o.z + y.z, o.w + y.w);
+        ov[it] = o;
+        so += o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
       }
       *reinterpret_cast<float4*>(h + (int64_t)m * d + c) = v;
       hv[it] = v;
       ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     }
   }
-  if (a == nullptr) return;
-  const float r = rsqrtf(block_sum(ss, red) / d + eps);
+  auto store = [&](T* dst, const float4 (&x)[4], float r) {
 #pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    const int c = (threadIdx.x + it * blockDim.x) * 4;
-    if (c < d) {
-      T* out = a + (int64_t)m * d + c;
-      Elem<T>::store(out, 0, hv[it].x * r);
-      Elem<T>::store(out, 1, hv[it].y * r);
-      Elem<T>::store(out, 2, hv[it].z * r);
-      Elem<T>::store(out, 3, hv[it].w * r);
+    for (int it = 0; it < 4; ++it) {
+      const int c = (threadIdx.x + it * blockDim.x) * 4;
+      if (c < d) {
+        T* out = dst + (int64_t)m * d + c;
+        Elem<T>::store(out, 0, x[it].x * r);
+        Elem<T>::store(out, 1, x[it].y * r);
+        Elem<T>::store(out, 2, x[it].z * r);
+        Elem<T>::store(out, 3, x[it].w * r);
+      }
     }
+  };
+  if (!before) {
+    if (a) store(a, hv, rsqrtf(block_sum(ss, red) / d + eps));
+    return;
   }
+  // both sums of squares in one pass through LDS
+  ss = wave_sum(ss);
+  so = wave_sum(so);
+  const int w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+  if (threadIdx.x % WAVE == 0) {
+    red[w] = ss;
+    red[16 + w] = so;
+  }
+  __syncthreads();
+  ss = so = 0.f;
+  for (int i = 0; i < nw; ++i) {
+    ss += red[i];
+    so += red[16 + i];
+  }
+  if (a) store(a, hv, rsqrtf(ss / d + eps));
+  store(before, ov, rsqrtf(so / d + eps));
 }
 
 // cos / sin of rotate-half RoPE for every slot position: tab[p][j] = (cos, sin)(p * theta^(-2j/Dh)),
@@ -532,7 +556,7 @@ static bool frag_ok(int pk, int M, int K, int dtype) {
 
 adt_status launch_embed_norm(const void* E, const int32_t* tok, int M, int d, float eps, float* h, void* a, int dtype,
                              hipStream_t st, const Branches& br, int a_pk, bool raw, const FwdScalars& fs) {
-  ADT_CHECK_ARG(a != nullptr && h != nullptr, ADT_E_ARG, "embed_norm: outputs");
+  ADT_CHECK_ARG((a != nullptr || dtype == ADT_F32) && h != nullptr, ADT_E_ARG, "embed_norm: outputs");
   ADT_CHECK_ARG(frag_ok(a_pk, M, d, dtype), ADT_E_SHAPE, "embed_norm: fragment layout of %d blocks for %d x %d", a_pk,
                 M, d);
   if (dtype == ADT_BF16 && d % 8 == 0 && d <= 4 * 8 * ROW_THREADS) {
@@ -629,12 +653,14 @@ adt_status launch_draft_input(const void* E, const int32_t* tok, const int32_t* 
 }
 
 adt_status launch_add_norm(const float* part, int splits, int M, int d, int assign, float eps, float* h, void* a,
-                           int dtype, hipStream_t st) {
+                           int dtype, hipStream_t st, void* before) {
   ADT_CHECK_ARG(d % 4 == 0 && d <= 16 * 1024, ADT_E_SHAPE, "add_norm: d=%d", d);
+  ADT_CHECK_ARG(!before || !assign, ADT_E_ARG, "add_norm: no earlier rows to normalise");
   int threads = (d / 4 + 63) / 64 * 64;   // one float4 column group per thread when d <= 4096
   if (threads > 1024) threads = 1024;
   if (threads < 64) threads = 64;
-  ADT_DISPATCH_T(dtype, add_norm_kernel<T><<<M, threads, 0, st>>>(part, splits, M, d, assign, eps, h, (T*)a));
+  ADT_DISPATCH_T(dtype, add_norm_kernel<T><<<M, threads, 0, st>>>(part, splits, M, d, assign, eps, h, (T*)a,
+                                                                      (T*)before));
   ADT_LAUNCH_CHECK();
   return ADT_OK;
 }

@@ -160,7 +160,7 @@ adt_status launch_gemm_nt(const void* X, int64_t ldx, const void* W, int64_t ldw
 size_t gemm_nt_part_elems(int M, int N, int K);
 // rows.hip
 // h = embedding rows, a = RMSNorm(h) (raw: h itself) in the model dtype (bf16: fragment
-// layout of a_pk row blocks when a_pk > 0, else row-major).
+// layout of a_pk row blocks when a_pk > 0, else row-major; fp32: may be null, for h alone).
 adt_status launch_embed_norm(const void* E, const int32_t* tok, int M, int d, float eps, float* h, void* a, int dtype,
                              hipStream_t st, const Branches& br = Branches{}, int a_pk = 0, bool raw = false, const FwdScalars& fs = {});
 // The residual projection's finish, one row per workgroup: y = sum over s < S of part[s][m][:]
@@ -180,8 +180,10 @@ adt_status launch_resid_add(const float* part, int S, int M, int d, int assign, 
 adt_status launch_draft_input(const void* E, const int32_t* tok, const int32_t* fsrc, const void* fa, const void* fb,
                               int M, int d, void* x, int dtype, hipStream_t st, const Branches& br = Branches{},
                               int x_pk = 0, const FwdScalars& fs = {}, const CatchUp& cu = {});
+// h[m] = the K-range sums of row m (assign), or added to it; a (if given) = RMSNorm(h[m]), before (if
+// given, not with assign) = RMSNorm of h[m] as it was.
 adt_status launch_add_norm(const float* part, int splits, int M, int d, int assign, float eps, float* h, void* a,
-                           int dtype, hipStream_t st);
+                           int dtype, hipStream_t st, void* before = nullptr);
 adt_status launch_rope_table(float2* tab, int positions, int Dh, double theta, hipStream_t st);
 adt_status launch_qkv_rope(const float* part, int splits, int M, int H, int Dh, const int32_t* pos,
                            const int32_t* slot0, const float2* rope, void* qout, void* kc, void* vc, int64_t stride_h,

@@ -45,3 +45,41 @@ def test_full_capture_buffer_launches_nothing(rt, dtype, call, short):
     for b, was in zip(bufs, before):
         assert torch.equal(b.view(torch.uint8), was.view(torch.uint8))
     assert sess.captured() == []
+
+
+def _normed(x):
+    x = x.double()
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + 1e-5)
+
+
+def test_fp32_view_shows_the_last_normed_activations(rt):
+    """act in the view of an fp32 session: the RMSNorm of the residual rows that entered the last
+    layer's MLP, after prompts (whose last forward is the draft's), expansions and verifies, and
+    the same after a graph replay."""
+    cfg, sess = _session(rt, "f32")
+    d = cfg.model.d_model
+    size = dict(resid_elems=1 << 20, xin_bytes=1 << 20, meta_elems=1 << 12)
+
+    def act(rows):
+        torch.cuda.synchronize()
+        return sess._ws(sess.view().act, rows * d, torch.float32).view(rows, d).cpu()
+
+    def check(what):
+        rec = sess.captured()[-1]
+        want = _normed(rec["resid"][-2])   # after the last layer's attention block
+        got = act(rec["rows"])
+        assert (got.double() - want).abs().max() <= 1e-5 * (1 + want.abs().max()), what
+        sess.set_capture(0)
+        return got
+
+    sess.set_capture(**size)
+    sess.prefill(synth.prefix_ids(cfg))
+    check("prefill")
+    for what, forward in (("expand", lambda: sess.expand(2, 3, 9)), ("verify", sess.verify)):
+        sess.set_capture(**size)
+        forward()
+        got = check(what)
+        sess._ws(sess.view().act, got.numel(), torch.float32).zero_()
+        for _ in range(2):   # captured into a graph, then replayed
+            forward()
+        assert torch.equal(act(got.shape[0]), got), what
