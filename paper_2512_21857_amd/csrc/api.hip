@@ -1194,15 +1194,11 @@ static adt_accept_cfg session_accept_cfg(const adt_session_s* s) {
   return c;
 }
 
-extern "C" adt_status adt_session_prefill(adt_session* s, const int32_t* prefix, int32_t* first_token, void* stream) {
-  ADT_CHECK_ARG(s && prefix, ADT_E_ARG, "prefill: null pointer");
-  ADT_CHECK_ARG(!s->prefilled, ADT_E_STATE, "prefill: already prefilled");
-  hipStream_t st = (hipStream_t)stream;
+// The forwards of a checked prompt, already in the pinned staging, and the first token (left in
+// the staging's bonus word).
+static adt_status prefill_forwards(adt_session* s, const int32_t* prefix, hipStream_t st) {
   const int P = s->P, nb = s->nb;
-  for (int i = 0; i < nb * P; ++i)
-    ADT_CHECK_ARG(prefix[i] >= 0 && prefix[i] < s->V, ADT_E_ARG, "prefill: id %d", prefix[i]);
   // ctok = the prompts of all branches, branch after branch
-  std::copy(prefix, prefix + nb * P, s->h_acc);   // pinned, at least 2 R >= nb P ids: no wait for the copy
   ADT_HIP(hipMemcpyAsync(s->ctok, s->h_acc, sizeof(int32_t) * nb * P, hipMemcpyHostToDevice, st));
   TRY(launch_prompt_rows(P, s->cpos, s->cfsrc, s->cmask, st));
   // Target and draft over the prompt in chunks of at most R rows (R / nb nodes).  Row p of the
@@ -1226,6 +1222,22 @@ extern "C" adt_status adt_session_prefill(adt_session* s, const int32_t* prefix,
   TRY(accept_impl(s->logits, s->V, s->V, s->tr.parent, s->tr.token, s->tr.allowed_rows, s->tr.n, 1, session_accept_cfg(s), 0,
                   s->tr.path, s->tr.nacc, s->tr.bonus, s->acc_ws, s->acc_ws_bytes, st));
   ADT_HIP(hipMemcpyAsync(s->h_acc + 2 * R + 1, s->tr.bonus, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  return ADT_OK;
+}
+
+extern "C" adt_status adt_session_prefill(adt_session* s, const int32_t* prefix, int32_t* first_token, void* stream) {
+  ADT_CHECK_ARG(s && prefix, ADT_E_ARG, "prefill: null pointer");
+  ADT_CHECK_ARG(!s->prefilled, ADT_E_STATE, "prefill: already prefilled");
+  hipStream_t st = (hipStream_t)stream;
+  const int P = s->P, nb = s->nb;
+  for (int i = 0; i < nb * P; ++i)
+    ADT_CHECK_ARG(prefix[i] >= 0 && prefix[i] < s->V, ADT_E_ARG, "prefill: id %d", prefix[i]);
+  std::copy(prefix, prefix + nb * P, s->h_acc);   // pinned, at least 2 R >= nb P ids: no wait for the copy
+  const adt_status e = prefill_forwards(s, prefix, st);
+  if (e != ADT_OK) {   // the copy may still be queued, and the staging is the next call's to write
+    (void)hipStreamSynchronize(st);
+    return e;
+  }
   TRY(sync_stream(st));
   const int32_t first = s->h_acc[2 * R + 1];
   s->tokens.assign(prefix, prefix + P);

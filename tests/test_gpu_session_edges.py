@@ -83,3 +83,24 @@ def test_fp32_view_shows_the_last_normed_activations(rt):
         for _ in range(2):   # captured into a graph, then replayed
             forward()
         assert torch.equal(act(got.shape[0]), got), what
+
+
+def test_failed_prefill_keeps_its_prompt(rt):
+    """A prefill that fails after its prompt was queued for the device, behind work that is still
+    running, has used that prompt and not the one of the call after it."""
+    from paper_2512_21857_amd import abi
+    cfg, sess = _session(rt, "f32")
+    m = cfg.model
+    first = synth.prefix_ids(cfg)
+    second = first[::-1].copy()
+    assert (first != second).any()
+    # room for the target forward over the prompt, none for the draft's
+    sess.set_capture(resid_elems=(2 * m.n_layers + 1) * cfg.prefix_len * m.d_model, xin_bytes=16, meta_elems=1 << 12)
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)
+    for prompt in (first, second):
+        with pytest.raises(abi.AdtError) as e:
+            sess.prefill(prompt)
+        assert e.value.code == abi.E_CAPACITY
+    recs = sess.captured()
+    assert len(recs) == 1 and recs[0]["tok"].tolist() == first.tolist()
