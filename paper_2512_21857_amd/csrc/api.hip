@@ -943,11 +943,18 @@ static adt_status resid_proj(adt_session_s* s, const void* X, const void* W, int
   return ADT_OK;
 }
 
+// Whether the attention of a forward of M nodes over L_pre + n_tail keys merges its key splits in
+// its own launch.  A captured forward keeps the choice, so it is part of its graph's key.
+static bool attn_merges(const adt_session_s* s, int M, int L_pre, int n_tail) {
+  return tree_attn_merges(s->nb, s->H, s->Dh, M, s->d.s_cap, L_pre + n_tail, s->dt);
+}
+static int64_t gkey_merge(int64_t key, bool merge) { return key < 0 ? key : key | (int64_t)merge << 56; }
+
 // Decoder layers over the nb * M rows of M tree nodes (branches interleaved node by node).
 // The final norm goes to final_out (row-major; bf16: act if null) and, with act_too (bf16),
-// also to act.
+// also to act.  merge: the attention's key splits merge in their launch (attn_merges).
 static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t* pos, int slot0, int L_pre, int n_tail,
-                             const uint64_t* mask, void* final_out, bool act_too, hipStream_t st) {
+                             const uint64_t* mask, void* final_out, bool act_too, bool merge, hipStream_t st) {
   const adt_model_s* m = s->m;
   const int dm = s->dm, H = s->H, Dh = s->Dh, F = s->F, dt = s->dt, nb = s->nb, rows = nb * M;
   const int64_t cache_sb = draft ? s->dcache_sb : s->tcache_sb;
@@ -967,7 +974,7 @@ static adt_status run_layers(adt_session_s* s, bool draft, int M, const int32_t*
     TRY(launch_tree_attn(s->q, kc, vc, cache_sb, stride_h, s->scal + SC_KV, s->scal + SC_NQ, s->scal + SC_TAIL, mask,
                          rl, nb, H, Dh, M, s->d.s_cap, scale, dt, s->att, s->attn_ws,
                          s->attn_ws_bytes, st, e >= 0 ? g_prof.ev[e] : nullptr, e >= 0 ? g_prof.ev[e + 1] : nullptr,
-                         s->attn_arrived));
+                         merge ? s->attn_arrived : nullptr));
     prof_done(e, ADT_PROF_ATTN, nb * (2.0 * L_pre * H * Dh * es + 4.0 * M * H * Dh * es) + 16.0 * M,
               4.0 * rows * (L_pre + n_tail) * H * Dh);
     return ADT_OK;
@@ -1086,6 +1093,7 @@ static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, co
                                  int64_t key = -1, int tok_boff = 0) {
   TRY(capt_check(s, false, M));
   const int pk = act_blocks(s, s->nb * M);
+  const bool merge = attn_merges(s, M, L_pre, n_tail);
   // The embedding rows and, in the same launch, the scalars that change from call to call (outside
   // the graph for their sake; a launch of their own took 2-4.6 us).  bf16: act takes the
   // raw embedding rows, which the first projection normalises; fp32 products read the residual itself.
@@ -1096,7 +1104,7 @@ static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, co
     TRY(capt_begin(s, false, M, L_pre, slot0, n_tail, tok, pos, mask, cs));
     // logits of every row read the final norm from act in the fragment layout
     const bool all = pk && lm_row0 == 0 && lm_rows == M;
-    TRY(run_layers(s, false, M, pos, slot0, L_pre, n_tail, mask, s->feat, all, cs));
+    TRY(run_layers(s, false, M, pos, slot0, L_pre, n_tail, mask, s->feat, all, merge, cs));
     if (all)
       TRY(lm_head(s, s->act, X_FRAG, lm_rows, s->logits, s->rawlog, cs));
     else if (lm_rows > 0)
@@ -1105,7 +1113,7 @@ static adt_status target_forward(adt_session_s* s, const int32_t* tok, int M, co
     s->capt_cur = -1;
     return ADT_OK;
   };
-  return key < 0 ? body(st) : run_graph(s, key, st, body);
+  return key < 0 ? body(st) : run_graph(s, gkey_merge(key, merge), st, body);
 }
 
 // Draft-head forward: FC over [embedding ; parent feature], one decoder layer, final norm
@@ -1118,6 +1126,7 @@ static adt_status draft_forward(adt_session_s* s, const int32_t* tok, const int3
   const int dm = s->dm, dt = s->dt, rows = s->nb * M;
   TRY(capt_check(s, true, M));
   const int pk = act_blocks(s, rows);
+  const bool merge = attn_merges(s, M, L_pre, n_tail);
   TRY(launch_draft_input(s->m->d.embed, tok, fsrc, fa, s->dfeat, rows, dm, s->xin, dt, st,
                          Branches{s->nb, tok_boff, 0}, pk, FwdScalars{s->scal, L_pre, M, n_tail, slot0}, cu));
   auto body = [&](hipStream_t cs) -> adt_status {
@@ -1136,7 +1145,7 @@ static adt_status draft_forward(adt_session_s* s, const int32_t* tok, const int3
       TRY(gemm_p(s->xin, 2 * dm, s->m->d.draft_fc, rows, dm, 2 * dm, dt, s->part, cs, e));
     }
     const bool all = pk && fout && lm_row0 == 0 && lm_rows == M;
-    TRY(run_layers(s, true, M, pos, slot0, L_pre, n_tail, mask, fout, all, cs));
+    TRY(run_layers(s, true, M, pos, slot0, L_pre, n_tail, mask, fout, all, merge, cs));
     if (all)
       TRY(lm_head(s, s->act, X_FRAG, lm_rows, lout, lraw, cs));
     else if (lm_rows > 0)
@@ -1144,7 +1153,7 @@ static adt_status draft_forward(adt_session_s* s, const int32_t* tok, const int3
     s->capt_cur = -1;
     return ADT_OK;
   };
-  return key < 0 ? body(st) : run_graph(s, key, st, body);
+  return key < 0 ? body(st) : run_graph(s, gkey_merge(key, merge), st, body);
 }
 
 // Debug builds: the invariant violations the kernels recorded since the last look (cleared).

@@ -850,6 +850,34 @@ static bool attn_use_blk(int B, int H, int nq_max) { return B * H >= 128 && nq_m
 // forwards) take the shared-block kernel with the keys split across workgroups instead.
 static bool attn_use_wg(int B, int H, int nq_max) { return B * H >= 128 && nq_max <= 16; }
 
+// Threads and keys per block of the shared-block kernel's instance for nq_max rows.
+struct BlkShape {
+  int threads, keys;
+};
+static BlkShape attn_blk_shape(int Dh, int nq_max) {
+  if (Dh == 128) return {nq_max <= 32 ? 4 * WAVE : AWG_W * WAVE, 64};
+  return {AWG_W * WAVE, nq_max <= 32 ? 128 : 64};
+}
+
+// Whether key splits merge in the launch that computes them, given arrival counters.  Keys that
+// fit one split need no merge, and the merge launch is saved (2-6 us a layer).  Otherwise one
+// workgroup merges each pair, and what counts is how often its threads go round the pair's
+// outputs (four each).  Once saves 0-1 us a layer against the merge launch; twice saves 0.2-1.4 us
+// where the launch has at least 200 workgroups (61 rows of 64 heads of 64: costs 0.4-0.9) and costs
+// 0.2-0.9 where it has 160 or fewer; more often costs 1-3 us (head size 128, 24-48 rows),
+// 4-5 (61 rows) and 11-14 (128 rows), which the merge launch spreads over every CU.  Measured with
+// 12-64 heads of 64 and 16-40 of 128, one and two branches, prefixes of 32-2200 keys.  7B 61-node
+// verify of two layers at 1050 keys: 272.3 us merged in the launch, 264.8 in a launch of its own.
+bool tree_attn_merges(int B, int H, int Dh, int nq_max, int kv_cap, int keys, int dtype) {
+  if (dtype != ADT_BF16 || attn_use_blk(B, H, nq_max) || attn_use_wg(B, H, nq_max)) return false;
+  const int S = attn_splits(B, H, kv_cap);
+  if (S == 1) return false;
+  const BlkShape k = attn_blk_shape(Dh, nq_max);
+  if (keys <= ATT_MIN_BLOCKS * k.keys) return true;
+  const int rounds = (nq_max * (Dh / 4) + k.threads - 1) / k.threads;
+  return rounds == 1 || (rounds == 2 && B * H * S >= 200);
+}
+
 // Upper bound over every kv_cap: the splits never exceed ceil(256 / (B*H)).
 size_t tree_attn_ws_bytes(int B, int H, int Dh, int nq_max, int kv_cap, int dtype) {
   (void)kv_cap;

@@ -86,6 +86,8 @@ adt_status launch_tree_attn(const void* q, const void* k, const void* v, int64_t
                             uint32_t* arrived = nullptr);
 // (arrived: B * H counters, zero before the first launch that gets them and left zero by every
 // one, for launches that follow one another in stream order: key splits merge in the same launch.)
+// Whether they should, for sequences of at most `keys` keys, their tree rows among them.
+bool tree_attn_merges(int B, int H, int Dh, int nq_max, int kv_cap, int keys, int dtype);
 
 // gemm.hip
 size_t packed_bytes(int total_rows, int K, int dtype);
