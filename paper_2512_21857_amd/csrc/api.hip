@@ -606,12 +606,10 @@ static void session_dims(adt_session_s* s, const adt_model_s* m, const adt_sessi
   s->KR = std::max(kh, 1);
   s->C = std::max(kw, kh + (dh - 1) * kh * kh);
   if (d->accept.mode == ADT_ACCEPT_MSS) s->C = std::max(s->C, R);   // every drawn child is kept
-  // fp32 projections write [rows][N] products for the row kernels; bf16 residual projections
-  // (O, down, draft FC) write up to GEMM_MAX_SPLITS K-range sums of [rows][d_model]
-  size_t pe = (size_t)GEMM_MAX_SPLITS * R * s->dm;
-  if (s->dt == ADT_F32)
-    for (int n : {3 * s->dm, s->dm, 2 * s->F, s->V}) pe = std::max(pe, (size_t)R * n);
-  s->part_elems = pe;
+  // Products finished by a launch of their own: up to GEMM_MAX_SPLITS K-range sums of [rows][d_model]
+  // (bf16 residual projections), or the fp32 QKV and last down products, [rows][3 d_model] at most.
+  static_assert(GEMM_MAX_SPLITS >= 3, "fp32 QKV products in part");
+  s->part_elems = (size_t)GEMM_MAX_SPLITS * R * s->dm;
 }
 
 static size_t session_layout(adt_session_s* s, char* base) {

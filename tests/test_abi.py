@@ -186,6 +186,35 @@ def test_accept_cfg_keeps_its_tensors_alive():
     assert q_logits[2, 3].item() == 11.0
 
 
+def test_fp32_workspace_follows_the_products_kept(L):
+    """An fp32 session's products of gate/up and of the LM head leave their launches finished, so
+    a wider MLP adds its 128 activation rows to the workspace and a larger vocabulary its logit
+    rows (128 of verifies, 1 + 3 * 4 of the draft) and acceptance scratch, and nothing else."""
+    from paper_2512_21857_amd import abi, runtime
+    from synth import get_config
+    cfg = get_config("tiny")
+    fake = C.c_void_p(1 << 20)
+    allowed = (C.c_int32 * (2 * cfg.n_image))(*([0, 1024] * cfg.n_image))
+    per_layer = C.cast((C.c_void_p * 3)(fake, fake, fake), C.POINTER(C.c_void_p))
+    desc = abi.SessionDesc(64, cfg.n_image, 512, fake, fake, fake, fake, C.cast(allowed, C.POINTER(C.c_int32)),
+                           runtime.sched_struct(cfg.sched, cfg.grid_w), runtime.accept_cfg("greedy"), None, 0, None, 0,
+                           1, 0, 0.0, None, 0)
+
+    def size(ffn, vocab):
+        m = abi.ModelDesc(2, 256, 4, 64, ffn, vocab, abi.F32, 10000.0, 1e-5, fake, fake, fake, per_layer, per_layer,
+                          per_layer, per_layer)
+        h = C.c_void_p()
+        assert L.adt_model_create(C.byref(m), C.byref(h)) == abi.OK
+        n = L.adt_session_workspace_size(h, C.byref(desc))
+        L.adt_model_destroy(h)
+        assert n > 0
+        return n
+
+    assert size(65536, 1056) - size(1024, 1056) == 128 * 4 * (65536 - 1024)
+    accept = L.adt_accept_workspace_size(65536) - L.adt_accept_workspace_size(1024)
+    assert size(1024, 65536) - size(1024, 1024) - 141 * 4 * (65536 - 1024) - accept < 256 * 4
+
+
 def test_capture_arguments(L):
     """Layer-by-layer record: a null session is refused, a record without its metadata buffer
     is refused, and a null session has no records."""
