@@ -381,10 +381,11 @@ __global__ __launch_bounds__(COMB_THREADS) void tree_attn_combine_kernel(
 }
 
 // fp32 path: one block per (query, head, sequence); scores staged in LDS.  Bound by the latency
-// of its loads (81 keys at 17 rows): a thread takes one key with sixteen dims in flight, then the
-// keys are dealt to 128 / (DH / 4) groups of threads of four dims each, whose sums meet in LDS
-// (7-8 us there in a trace, about what a load per dim and one thread per dim over every key
-// took, which grows with every key).
+// of its loads: a thread takes one key with sixteen dims in flight, then the keys are dealt to
+// 128 / (DH / 4) groups of threads of four dims each, whose sums meet in LDS.  A load per dim and
+// one thread per dim over every key had taken, traced at prefixes of 64 / 300 / 1000 / 2300 keys and
+// 17-20 rows: 7.3 / 16.3 / 42.5 / 152.9 us (4 heads of 64; now 6.0 / 9.2 / 17.7 / 46.6) and
+// 8.8 / 37.0 / 103.7 / 234.9 (16 heads of 128; now 7.7 / 20.5 / 52.9 / 115.1).
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int F32_THREADS = 128;
 __global__ __launch_bounds__(F32_THREADS) void tree_attn_f32_kernel(
@@ -414,15 +415,13 @@ __global__ __launch_bounds__(F32_THREADS) void tree_attn_f32_kernel(
     if (k < L || tail_visible(w0, w1, k - L)) {
       float acc = 0.f;
       const float* kr = kb + (int64_t)k * DH;
-      int d = 0;
-      for (; d + 16 <= DH; d += 16) {
+      for (int d = 0; d < DH; d += 16) {
         f32x4 t[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) t[j] = *reinterpret_cast<const f32x4_a4*>(kr + d + 4 * j);
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc += qs[d + j] * t[j / 4][j % 4];
       }
-      for (; d < DH; ++d) acc += qs[d] * kr[d];
       v = acc * scale;
     }
     sc[k] = v;
@@ -443,40 +442,29 @@ __global__ __launch_bounds__(F32_THREADS) void tree_attn_f32_kernel(
   sum = block_sum(sum, red + 8);
   __syncthreads();
   float* orow = out + (rl.q_row(b, qr) * H + h) * DH;
-  const int per = DH / 4, groups = DH % 4 == 0 && per <= F32_THREADS ? F32_THREADS / per : 0;
-  if (groups) {
-    __shared__ f32x4 pv[F32_THREADS];
-    const int grp = tid / per, d = tid % per * 4;
-    f32x4 a0{0.f, 0.f, 0.f, 0.f}, a1 = a0, a2 = a0, a3 = a0;
-    if (grp < groups) {
-      const float* vp = vb + d;
-      int k = grp;
-      for (; k + 3 * groups < total; k += 4 * groups) {
-        const f32x4 v0 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)k * DH);
-        const f32x4 v1 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)(k + groups) * DH);
-        const f32x4 v2 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)(k + 2 * groups) * DH);
-        const f32x4 v3 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)(k + 3 * groups) * DH);
-        a0 += sc[k] * v0;
-        a1 += sc[k + groups] * v1;
-        a2 += sc[k + 2 * groups] * v2;
-        a3 += sc[k + 3 * groups] * v3;
-      }
-      for (; k < total; k += groups) a0 += sc[k] * f32x4(*reinterpret_cast<const f32x4_a4*>(vp + (int64_t)k * DH));
-    }
-    pv[tid] = (a0 + a1) + (a2 + a3);
-    __syncthreads();
-    if (grp == 0) {
-      f32x4 y = pv[tid];
-      for (int g = 1; g < groups; ++g) y += pv[g * per + tid];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) orow[d + e] = y[e] / sum;
-    }
-    return;
+  __shared__ f32x4 pv[F32_THREADS];
+  const int per = DH / 4, groups = F32_THREADS / per, grp = tid / per, d = tid % per * 4;
+  f32x4 a0{0.f, 0.f, 0.f, 0.f}, a1 = a0, a2 = a0, a3 = a0;
+  const float* vp = vb + d;
+  int k = grp;
+  for (; k + 3 * groups < total; k += 4 * groups) {
+    const f32x4 v0 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)k * DH);
+    const f32x4 v1 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)(k + groups) * DH);
+    const f32x4 v2 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)(k + 2 * groups) * DH);
+    const f32x4 v3 = *reinterpret_cast<const f32x4_a4*>(vp + (int64_t)(k + 3 * groups) * DH);
+    a0 += sc[k] * v0;
+    a1 += sc[k + groups] * v1;
+    a2 += sc[k + 2 * groups] * v2;
+    a3 += sc[k + 3 * groups] * v3;
   }
-  for (int d = tid; d < DH; d += blockDim.x) {
-    float acc = 0.f;
-    for (int k = 0; k < total; ++k) acc += sc[k] * vb[(int64_t)k * DH + d];
-    orow[d] = acc / sum;
+  for (; k < total; k += groups) a0 += sc[k] * f32x4(*reinterpret_cast<const f32x4_a4*>(vp + (int64_t)k * DH));
+  pv[tid] = (a0 + a1) + (a2 + a3);
+  __syncthreads();
+  if (grp == 0) {
+    f32x4 y = pv[tid];
+    for (int g = 1; g < groups; ++g) y += pv[g * per + tid];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) orow[d + e] = y[e] / sum;
   }
 }
 
@@ -978,6 +966,8 @@ adt_status launch_tree_attn(const void* q, const void* k, const void* v, int64_t
                 ADT_E_ARG, "tree_attn: fragment-layout output of %d row blocks (bf16, rows of a multiple of 32 values)",
                 rl.o_pk);
   if (dtype == ADT_F32) {
+    // sixteen dims a load, and threads dealt to whole groups of Dh / 4
+    ADT_CHECK_ARG(Dh == 64 || Dh == 128, ADT_E_SHAPE, "tree_attn f32: head_dim %d", Dh);
     const size_t sm = (size_t)(Dh + kv_cap) * sizeof(float);
     ADT_CHECK_ARG(sm <= 60 * 1024, ADT_E_CAPACITY, "tree_attn f32: kv_cap %d too large for LDS scores", kv_cap);
     dim3 grid(nq_max, H, B);
