@@ -202,7 +202,7 @@ __device__ __forceinline__ float sumsq8(bf16x8 v, float s) {
 // workgroup, KC = k-tiles per load round.
 // Workgroup b takes column block b / S and K range b % S; wave w takes the w-th eighth of the
 // range.  Rounds are double-buffered: round r + 1's fragments are requested before round r's
-// MFMAs, so one round stays in flight per wave.  With stagger the wave starts its rounds at an
+// MFMAs, so one round stays in flight per wave.  A wave starts its rounds at an
 // offset that depends on the workgroup (wrapping around its chunk), so the waves of different
 // CUs do not read the same input lines at the same time; the sum order stays fixed per tile.
 // Loads past the wave's range are clamped to its last k-tile and their products discarded.
@@ -537,19 +537,23 @@ __global__ __launch_bounds__(TILE_THREADS, 2) void gemm_rows_dma_kernel(const ui
 }
 
 // ----------------------------------------------------------------------------- fp32 MFMA
-// Unfused fp32 path (row kernels finish the layer), on v_mfma_f32_16x16x4f32 (fp32 products and
+// fp32 products on v_mfma_f32_16x16x4f32 (fp32 products and
 // sums).  A small fp32 model's product is bound by latency, not by bytes (0.25-2 MB of weights
 // that stay in L2), so a workgroup takes one 16-column tile and MR 16-row blocks, its eight
 // waves split K, and every load of a wave's K range (up to U steps of 16) is in flight before
 // its first product.  Lane (lq, g) holds four consecutive k of W row lq and of X row lq, one
 // accumulator per element and per odd or even step, so the MFMA chains are K / 256 long (the
-// sums stay as short as a lane-strided sum's); accumulators, then waves, are added pairwise.  One wave per column with the rows read one by one had taken 24-72 us a
-// launch at 17 rows (K 256 and 1024): 377 -> 104 us for the two-layer model's 17-row forward.
+// sums stay as short as a lane-strided sum's); accumulators, then waves, are added pairwise.
+// One wave per column with the rows read one by one had taken 24-72 us a launch at 17 rows (K 256
+// and 1024): 377 -> 104 us for the two-layer model's 17-row forward; two layers of d 1280 and 2048
+// (FFN 3584, 5632) at 1 / 17 / 128 rows 310 / 1591 / 10921 -> 136 / 199 / 530 us and
+// 568 / 3022 / 20139 -> 323 / 431 / 1166.
 // W and X rows need 4-byte alignment only; K is a multiple of 16; rows past M or N repeat the last.
 // Epilogues as in the bf16 path, each instead of a launch of 2.5-5 us: act takes silu(gate) up of the
 // gate/up product, resid is added to (assign: set), and with NORM the rows are un-normalised
 // and scaled afterwards by their RMSNorm factor, whose sum of squares the waves take from the
-// fragments they multiply (two-layer tiny model's 17-row forward 80.4 -> 75.1 us).
+// fragments they multiply (two-layer tiny model's 17-row forward 80.4 -> 75.1 us).  Without one the
+// product goes to part: logits as they are, QKV for RoPE, the last down product for the final norm.
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int MR, int U, bool NORM>
@@ -723,6 +727,10 @@ adt_status launch_pack(const void* const* srcs, const int32_t* rows, int n_src, 
 // and the K ranges that fill the CUs (LlamaGen-XL down 17.3 -> 8.1 us with six; at K = 1280 the
 // separate finish costs what the split gains).  Two to three tiles per CU: T = 3 in one round of
 // the CUs on the register kernel (QKV 51 -> 32 us at 122 rows, 44 -> 29 at 90).
+// The lines lie between the shapes timed alone (K 4096 and 11008 of 256 tiles, 1280 and 3584 of 80);
+// the draft FC's K of 8192 keeps one K range.  Other widths and K were timed in whole models only:
+// two layers of d 768-5120 (FFN 2816-13824, LM heads of 8192-65536) at 65-128 rows take 0.67-0.91 of
+// what they took before these plans, the row groups below and the attention's merge.
 static RowsPlan gemm_rows_plan_all(int M, int N, int K, bool partial, bool wide, bool frag) {
   const int mt = (M + 15) / 16, tiles = N / 16, KT = K / 32;
   if (mt > 4 && frag) {

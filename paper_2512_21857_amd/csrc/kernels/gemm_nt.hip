@@ -147,10 +147,13 @@ __global__ __launch_bounds__(NT_THREADS) void gemm_nt_kernel(const uint16_t* __r
 // next stage's first fragments are read while the second half's MFMAs run.  One DMA tile is
 // issued after every second of those MFMAs, from a scalar base: four in a row behind the barrier,
 // each with a 64-bit lane address, held the wave's MFMAs back (976 x 22016 x 4096 in a stream of
-// calls 193.3 -> 188.3 us).  At M = 976 all of these measured the same or slower: X in fragment
-// order, four waves of 128 x 128 (a third fewer LDS reads), two K groups in a 128 x 128 block; a
-// library product of the same operands takes 197.5 us (bf16 result).  The DMA and
-// the waits are inline assembly because the compiler, which cannot tell LDS slots apart,
+// calls 193.3 -> 188.3 us).  At M = 976 these measured the same or slower: four waves
+// of 128 x 128 (a third fewer LDS reads), two K groups in a 128 x 128 block, and for 22016 columns X in
+// fragment order (195.6), which for 4096 x 4096 was faster in that probe (47.8 -> 43.2; not built:
+// the rows come row-major).  The library's product of the same operands, with a bf16 result, is ahead
+// (calls back to back, inputs changing): 163-171 us beside 194-200 at 22016 columns, 40 beside 54 at
+// 4096; the split last round and its reduce are 36 % of the time for 26 % of the work of the former.
+// The DMA and the waits are inline assembly because the compiler, which cannot tell LDS slots apart,
 // would otherwise wait for every DMA in flight before each LDS read.
 constexpr int DMA_NSTAGE = 5;
 

@@ -1,6 +1,7 @@
 // Row-wise kernels of the forwards and of the cache bookkeeping: embedding with its norm, the
-// finish of a residual projection (K-range sums, residual add, the next norm), the fp32 path's finishing steps after each projection (residual add + RMSNorm, RoPE + KV
-// append, SwiGLU, logits), feature gathers, KV compaction and ancestor masks.  Each kernel
+// finish of a residual projection (K-range sums, residual add, the next norm), finishing steps of the
+// fp32 path (RoPE + KV append, the final norm) and of the batched products (residual add + RMSNorm,
+// RoPE + KV append, SwiGLU), feature gathers, KV compaction and ancestor masks.  Each kernel
 // handles whole rows (at most 128 tree rows per launch), so they are latency-bound and kept
 // as simple as possible.
 #include <algorithm>

@@ -97,7 +97,7 @@ adt_status launch_pack(const void* const* srcs, const int32_t* rows, int n_src, 
 // owns T 16-column tiles and one of S contiguous K ranges; its eight waves split that range
 // and their partial tiles are summed in LDS in wave order.  With S = 1 the finished tile
 // runs the epilogue; EPI_PART stores the S range sums instead, for resid_norm to add in
-// range order.  T and S come from gemm_rows_plan.
+// range order.  T and S come from gemm_rows_plan, or gemm_resid_plan for EPI_RESID.
 enum : int { EPI_STORE = 1, EPI_PART = 2, EPI_QKV = 3, EPI_SWIGLU = 4, EPI_RESID = 5 };
 struct GemmEpi {
   int mode = EPI_STORE;
@@ -126,14 +126,14 @@ struct GemmEpi {
   uint16_t* act = nullptr;
   int act_pk = 0;
   // EPI_RESID (one K range): resid[m][n] (fp32, [M][N]) += Y (assign: = Y), then act[m][n] =
-  // the new residual in bf16, layout act_pk
+  // the new residual in bf16, layout act_pk (fp32 products: no act)
   float* resid = nullptr;
   int assign = 0;
-  // norm_eps > 0 (not with EPI_PART or EPI_RESID): the input rows are un-normalised and every
+  // norm_eps > 0 (bf16: not with EPI_PART or EPI_RESID): the input rows are un-normalised and every
   // output row is scaled by 1 / sqrt(mean of its input row's squares + norm_eps), the RMSNorm
-  // (unit gain) of the bf16 rows the kernel reads
+  // (unit gain) of the rows the kernel reads
   float norm_eps = 0.f;
-  bool norm = false;   // fp32 products: the norm whatever norm_eps is
+  bool norm = false;   // fp32 products: whether to normalise, whatever norm_eps is
 };
 struct RowsPlan {
   int T, S;       // at most T 16-column tiles per workgroup, S K ranges
@@ -145,8 +145,8 @@ RowsPlan gemm_rows_plan(int M, int N, int K, bool partial, bool wide = false, bo
 // The plan of a residual projection; S = 1: EPI_RESID, else EPI_PART and the finish by row kernels.
 RowsPlan gemm_resid_plan(int M, int N, int K);
 constexpr int GEMM_MAX_SPLITS = 8;
-// fp32: part[M][N] = X . W^T (consumed by the row kernels).  bf16: the kernel above with the
-// epilogue epi; *splits (if given) gets S.  bf16 X is row-major with leading dimension ldx, or
+// fp32: part[M][N] = X . W^T, or with EPI_SWIGLU and EPI_RESID the epilogue's own output.  bf16: the
+// kernel above with the epilogue epi; *splits (if given) gets S.  bf16 X is row-major with leading dimension ldx, or
 // with ldx == X_FRAG in the fragment layout of (M + 15) / 16 row blocks.
 constexpr int X_FRAG = 0;
 adt_status launch_gemm(const void* X, int ldx, const void* Wp, int M, int N, int K, int dtype, float* part,

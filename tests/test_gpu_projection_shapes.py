@@ -84,6 +84,15 @@ def test_verify_bf16_65_to_128_rows(rt, heads, ffn, vocab, n):
     _check_verify(rt, cfg, n, by_row=d > 2048)
 
 
+@pytest.mark.parametrize("vocab,n", [(32784, 65), (49168, 100), (65536, 128)])
+def test_verify_bf16_wide_lm_head_65_to_128_rows(rt, vocab, n):
+    """LM heads of more than 2048 column tiles at five to eight row blocks: two workgroups a CU of
+    four to five, six to seven and eight tiles."""
+    cfg = synth.shrink(synth.get_config("llamagen_xl"), n_layers=1, d_model=128, n_heads=2, ffn=96, vocab=vocab)
+    cfg = dataclasses.replace(cfg, prefix_len=70, img_hi=vocab, prefix_hi=vocab, grid_h=8, grid_w=16)
+    _check_verify(rt, cfg, n)
+
+
 @pytest.mark.parametrize("heads,ffn,n", [(2, 96, 17), (2, 96, 50), (20, 3584, 33), (20, 3584, 61), (20, 3584, 90),
                                          (20, 3584, 113)])
 def test_verify_bf16_row_groups(rt, heads, ffn, n):
