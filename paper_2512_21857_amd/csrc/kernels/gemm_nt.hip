@@ -144,15 +144,17 @@ __global__ __launch_bounds__(NT_THREADS) void gemm_nt_kernel(const uint16_t* __r
 // half's eight MFMAs run; each wave waits for its own DMA of stage kt+1 (the NSTAGE-3 newer
 // stages stay in flight) and one barrier publishes it; the DMA of stage kt+NSTAGE-1 then
 // refills the slot of stage kt-1, whose fragments every wave consumed before that barrier; the
-// next stage's first fragments are read while the second half's MFMAs run.  One DMA tile is
-// issued after every second of those MFMAs, from a scalar base: four in a row behind the barrier,
-// each with a 64-bit lane address, held the wave's MFMAs back (976 x 22016 x 4096 in a stream of
-// calls 193.3 -> 188.3 us).  At M = 976 these measured the same or slower: four waves
-// of 128 x 128 (a third fewer LDS reads), two K groups in a 128 x 128 block, and for 22016 columns X in
-// fragment order (195.6), which for 4096 x 4096 was faster in that probe (47.8 -> 43.2; not built:
-// the rows come row-major).  The library's product of the same operands, with a bf16 result, is ahead
-// (calls back to back, inputs changing): 163-171 us beside 194-200 at 22016 columns, 40 beside 54 at
-// 4096; the split last round and its reduce are 36 % of the time for 26 % of the work of the former.
+// next stage's first fragments are read while the second half's MFMAs run.  The DMA goes out from a
+// scalar base, in the wide blocks one tile after every second of those MFMAs: four in a row behind
+// the barrier held the wave's MFMAs back (976 x 22016 x 4096 in a stream of calls 193.3 -> 188.3 us).
+// The 128 x 128 blocks issue all four at once: few rows wait for the loads and not for the MFMAs
+// (40 x 8192 x 4096 22.0 us, spread 22.7; 40 x 1280 x 3584 15.6 and 15.8; 976 rows the same).
+// At M = 976 these measured the same or slower: four waves of 128 x 128 (a third fewer LDS reads), two
+// K groups in a 128 x 128 block, and for 22016 columns X in fragment order (195.6), which for
+// 4096 x 4096 was faster in that probe (47.8 -> 43.2; not built: the rows come row-major).  The
+// library's product of the same operands, with a bf16 result, is ahead (calls back to back, inputs
+// changing): 163-171 us beside 194-200 at 22016 columns, 40 beside 54 at 4096; the split last round
+// and its reduce are 36 % of the time for 26 % of the work of the former.
 // The DMA and the waits are inline assembly because the compiler, which cannot tell LDS slots apart,
 // would otherwise wait for every DMA in flight before each LDS read.
 constexpr int DMA_NSTAGE = 5;
@@ -180,6 +182,7 @@ __global__ __launch_bounds__(WN * WM * WAVE) void gemm_nt_dma_kernel(const uint1
   constexpr int WTN = BN / WN, WTM = BM / WM, NB = WTN / 32, MB = WTM / 32;
   static_assert(TILES == 4 * WAVES && (BN / 16) % 4 == 0 && NB >= 1 && MB >= 1, "four DMA tiles per wave");
   constexpr int D = NSTAGE - 1;   // stages in flight ahead of the one being multiplied
+  constexpr bool SPREAD = BN > 128;   // a stage's DMA issued tile by tile between the MFMAs
   __shared__ __attribute__((aligned(1024))) uint16_t lds[NSTAGE * SLOT / 2];
   // XCD-aware order: workgroup b runs on XCD b % 8; each XCD takes a contiguous range of
   // tiles (row blocks fastest), so the row blocks that share a W block meet in one L2
@@ -262,6 +265,7 @@ __global__ __launch_bounds__(WN * WM * WAVE) void gemm_nt_dma_kernel(const uint1
     __builtin_amdgcn_sched_group_barrier(0x008, NB * MB, 0);
     if constexpr (D == 3) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+    if constexpr (!SPREAD) issue(kt + D);
     frags(kt + 1, 0, a0, b0);   // past the last stage: a stale slot, never used
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -269,7 +273,7 @@ __global__ __launch_bounds__(WN * WM * WAVE) void gemm_nt_dma_kernel(const uint1
       acc[j / MB][j % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[j / MB], b1[j % MB], acc[j / MB][j % MB], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (j == (i + 1) * NB * MB / 4 - 1) {
+        if (SPREAD && j == (i + 1) * NB * MB / 4 - 1) {
           __builtin_amdgcn_sched_barrier(0);
           issue1(kt + D, i);
           __builtin_amdgcn_sched_barrier(0);
