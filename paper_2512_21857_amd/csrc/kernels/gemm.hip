@@ -9,11 +9,13 @@
 // partial tiles in LDS in wave order (deterministic; no workgroup waits on another).  T and
 // S are chosen so that about one workgroup lands on each CU with as many columns as its
 // registers allow: every workgroup reads the M input rows of its K range, so more columns
-// per workgroup mean fewer re-reads of the input per weight byte.  The input rows are the
-// bf16 activations the previous step stored (the residual projections' finish writes the
-// next RMSNorm output).  With S = 1 the finished tile runs a fused epilogue (RoPE with the
-// K/V cache append, SwiGLU, or a plain store); residual projections store their K-range
-// sums, and resid_norm adds them in range order.
+// per workgroup mean fewer re-reads of the input per weight byte; narrow products at 17-128 rows
+// divide the rows among workgroups instead.  The input rows are bf16 in the fragment layout (a
+// product may normalise them itself).  With S = 1 the finished tile runs a fused epilogue (RoPE with
+// the K/V cache append, SwiGLU, the residual add, or a plain store); K-range sums are stored, and
+// resid_add or resid_norm adds them in range order.  At 65-128 rows wide products, and K ranges
+// of long ones, take a kernel that stages both operands in LDS.  fp32 products have a kernel of
+// their own.
 #include <hip/hip_ext.h>
 
 #include <algorithm>

@@ -153,8 +153,8 @@ __global__ __launch_bounds__(NT_THREADS) void gemm_nt_kernel(const uint16_t* __r
 // K groups in a 128 x 128 block, and for 22016 columns X in fragment order (195.6), which for
 // 4096 x 4096 was faster in that probe (47.8 -> 43.2; not built: the rows come row-major).  The
 // library's product of the same operands, with a bf16 result, is ahead (calls back to back, inputs
-// changing): 163-171 us beside 194-200 at 22016 columns, 40 beside 54 at 4096; the split last round
-// and its reduce are 36 % of the time for 26 % of the work of the former.
+// changing): 163-171 us beside 194-200 at 22016 columns, 40 beside 54 at 4096; of the former,
+// the split last round and its reduce are 37 % (traced 143 + 73 + 11 us) for 26 % of the work.
 // The DMA and the waits are inline assembly because the compiler, which cannot tell LDS slots apart,
 // would otherwise wait for every DMA in flight before each LDS read.
 constexpr int DMA_NSTAGE = 5;
