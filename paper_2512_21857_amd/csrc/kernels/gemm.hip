@@ -731,8 +731,8 @@ adt_status launch_pack(const void* const* srcs, const int32_t* rows, int n_src, 
 // the CUs on the register kernel (QKV 51 -> 32 us at 122 rows, 44 -> 29 at 90).
 // The lines lie between the shapes timed alone (K 4096 and 11008 of 256 tiles, 1280 and 3584 of 80);
 // the draft FC's K of 8192 keeps one K range.  Other widths and K were timed in whole models only:
-// two layers of d 768-5120 (FFN 2816-13824, LM heads of 8192-65536) at 65-128 rows take 0.67-0.91 of
-// what they took before these plans, the row groups below and the attention's merge.
+// one or two layers of d 768-6144 (FFN 2816-16384, LM heads of 8192-65536) at 65-128 rows take
+// 0.65-0.86 of what they took before these plans, the row groups below and the attention's merge.
 static RowsPlan gemm_rows_plan_all(int M, int N, int K, bool partial, bool wide, bool frag) {
   const int mt = (M + 15) / 16, tiles = N / 16, KT = K / 32;
   if (mt > 4 && frag) {
